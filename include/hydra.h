@@ -138,8 +138,8 @@ hydra_status hydra_lora_linear_ws(const uint16_t* x, const uint16_t* W, const ui
  *   s                     HOST array of G scales
  * Member i computes exactly what hydra_lora_linear(x[i], W[i], A[i], B[i], s[i],
  * M, N, K, r, y_off[i], y_on[i]) computes.  Each member needs at least one
- * output.  M <= 16 runs one launch for the whole group; larger M runs the GEMM
- * once per member.  Errors as in hydra_lora_linear; HYDRA_ERR_SHAPE for G out
+ * output.  M <= 16 runs one launch for the whole group; larger M one launch
+ * too where the GEMM takes its smaller tiles, else the GEMM once per member.  Errors as in hydra_lora_linear; HYDRA_ERR_SHAPE for G out
  * of range.
  */
 hydra_status hydra_lora_linear_group(int64_t G, const uint16_t* const* x, const uint16_t* const* W,

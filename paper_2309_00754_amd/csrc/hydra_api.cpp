@@ -124,8 +124,11 @@ hydra_status group_check(int64_t G, const uint16_t* const* x, const uint16_t* co
   return HYDRA_OK;
 }
 
-// M > 16, padded rank <= 64: one dual GEMM per member.
+// M > 16, padded rank <= 64: the members in one launch on the smaller tiles,
+// else one dual GEMM per member.
 hydra_status group_gemm(const hydra::GroupArgs& g, hipStream_t st) {
+  const int tile = hydra::gemm_mid_tile(g.M, g.N, g.K);
+  if (tile >= 0) return from_hip(hydra::launch_lora_gemm_mid(g, nullptr, nullptr, 0, tile, st));
   for (int i = 0; i < g.G; ++i) {
     hydra::LinearArgs a{};
     a.x = g.x[i];
@@ -268,6 +271,13 @@ hydra_status hydra_lora_linear_group_ws(int64_t G, const uint16_t* const* x, con
   if (together && nj > 1) {
     if (hydra::launch_lora_tpre_multi(ta, nj, rp, st) != hipSuccess) return HYDRA_ERR_HIP;
     int j = 0;
+    const int tile = hydra::gemm_mid_tile(g.M, g.N, g.K);
+    if (tile >= 0) {  // every member in one launch
+      const uint16_t* ts[hydra::kMaxGroup] = {};
+      for (int i = 0; i < g.G; ++i)
+        if (la[i].r > 0 && la[i].y_on) ts[i] = ta[j++].ts;
+      return from_hip(hydra::launch_lora_gemm_mid(g, ts, g.B, rp, tile, st));
+    }
     for (int i = 0; i < g.G; ++i) {
       const hydra::LinearArgs& a = la[i];
       const hipError_t e = a.r > 0 && a.y_on ? hydra::launch_lora_gemm_slabs(a, ta[j++].ts, a.B, rp, st)

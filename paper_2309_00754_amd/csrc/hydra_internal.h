@@ -220,6 +220,15 @@ constexpr int kGemmTileM = 128;
 constexpr int kGemmTileN = 256;
 constexpr int kGemmThreads = 512;
 
+// The smaller tile of lora_gemm_mid.hip that serves M rows, N outputs and K
+// inputs, or -1 where the 128 x 256 tile is the better one.  It depends on
+// these sizes alone: every entry point sums an output in the same order.
+int gemm_mid_tile(int M, int N, int K);
+// The members of ga on that tile, in one launch.  With ts / bp the
+// LoRA update comes from the pre-pass (rp_pre the padded rank, ts[i] null: no
+// adapter); without, from A and B (padded rank up to 64).
+hipError_t launch_lora_gemm_mid(const GroupArgs& ga, const uint16_t* const* ts, const uint16_t* const* bp, int rp_pre,
+                                int tile, hipStream_t stream);
 hipError_t launch_lora_gemm(const LinearArgs& a, hipStream_t stream);
 // The same with the LoRA update from the pre-pass: ts [M x 2 RP] and bp [N x RP]
 // bf16 workspace (RP = padded rank of a.r, up to 128).

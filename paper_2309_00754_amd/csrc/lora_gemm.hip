@@ -547,22 +547,44 @@ hipError_t launch(const GemmArgs& g, int rp, bool tpre, hipStream_t stream) {
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
+GroupArgs group_of(const LinearArgs& a) {
+  GroupArgs g{};
+  g.x[0] = a.x;
+  g.W[0] = a.W;
+  g.A[0] = a.r > 0 ? a.A : nullptr;
+  g.B[0] = a.r > 0 ? a.B : nullptr;
+  g.y_off[0] = a.y_off;
+  g.y_on[0] = a.y_on;
+  g.s[0] = a.s;
+  g.G = 1;
+  g.M = a.M;
+  g.N = a.N;
+  g.K = a.K;
+  g.r = a.r;
+  return g;
+}
+
 }  // namespace
 
 hipError_t launch_lora_gemm(const LinearArgs& a, hipStream_t stream) {
+  const int rp = a.y_on ? padded_rank(a.r) : 0;
+  if (rp > 64) return hipErrorInvalidValue;  // needs the pre-pass workspace
+  const int tile = gemm_mid_tile(a.M, a.N, a.K);
+  if (tile >= 0) return launch_lora_gemm_mid(group_of(a), nullptr, nullptr, 0, tile, stream);
   GemmArgs g{};
   g.lin = a;
   g.ntm = (a.M + BM - 1) / BM;
   g.ntn = (a.N + BN - 1) / BN;
   g.vec4 = (a.N % 4 == 0) && (!a.y_off || aligned16(a.y_off)) && (!a.y_on || aligned16(a.y_on));
-  const int rp = a.y_on ? padded_rank(a.r) : 0;
-  if (rp > 64) return hipErrorInvalidValue;  // needs the pre-pass workspace
   return launch(g, rp, false, stream);
 }
 
 hipError_t launch_lora_gemm_tpre(const LinearArgs& a, uint16_t* ts, uint16_t* bp, float* part, hipStream_t stream) {
   const int rp = a.y_on ? padded_rank(a.r) : 0;
-  if (rp == 0) return launch_lora_gemm(a, stream);
+  // On the smaller tiles T in the tile (up to padded rank 64) costs less than
+  // the pre-pass's two launches (10-14 us): 333 x 2048 x 2000 at rank 64 takes
+  // 16.6 us in one launch against 11.7 + 12.
+  if (rp <= 64 && (rp == 0 || gemm_mid_tile(a.M, a.N, a.K) >= 0)) return launch_lora_gemm(a, stream);
   TpreArgs t{};
   t.x = a.x;
   t.A = a.A;
@@ -578,19 +600,13 @@ hipError_t launch_lora_gemm_tpre(const LinearArgs& a, uint16_t* ts, uint16_t* bp
   const uint16_t* bp_used = nullptr;
   hipError_t e = launch_lora_tpre(t, rp, &bp_used, stream);
   if (e != hipSuccess) return e;
-  GemmArgs g{};
-  g.lin = a;
-  g.ntm = (a.M + BM - 1) / BM;
-  g.ntn = (a.N + BN - 1) / BN;
-  g.vec4 = (a.N % 4 == 0) && (!a.y_off || aligned16(a.y_off)) && aligned16(a.y_on);
-  g.ts = ts;
-  g.bp = bp_used;
-  g.nls = (2 * rp + BK - 1) / BK;
-  return launch(g, rp, true, stream);
+  return launch_lora_gemm_slabs(a, ts, bp_used, rp, stream);
 }
 
 hipError_t launch_lora_gemm_slabs(const LinearArgs& a, const uint16_t* ts, const uint16_t* bp, int rp,
                                   hipStream_t stream) {
+  const int tile = gemm_mid_tile(a.M, a.N, a.K);
+  if (tile >= 0) return launch_lora_gemm_mid(group_of(a), &ts, &bp, rp, tile, stream);
   GemmArgs g{};
   g.lin = a;
   g.ntm = (a.M + BM - 1) / BM;

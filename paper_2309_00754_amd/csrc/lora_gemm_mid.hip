@@ -1,0 +1,555 @@
+// Dual-path LoRA GEMM for row counts whose 128 x 256 tiles would leave most of
+// the 256 CUs idle (prompts, mini-batches, generation batches above 16 rows).
+// Same function as lora_gemm_kernel on smaller tiles (GemmMid below): the
+// LoRA-off output x W^T and the LoRA-on output x W^T + s (x A^T) B^T from one
+// pass over W (Sec. 3, "Dynamic LoRA" and "Stage 2: Hydra-PPO").
+//
+// What bounds a small tile is the copy of its operands into LDS (about
+// 64 B/clk per CU) and the latency of each K slab, not the matrix cores.  So:
+//  * one workgroup of 8 waves per tile; the waves that share a sub-tile split
+//    every K slab among them (KS ways), which keeps the sub-tile of a wave, and
+//    with it the number of MFMAs per LDS byte, large on a small tile;
+//  * every wave issues its share of the copies (buffer_load ... lds) for the
+//    slab NS ahead, reads the fragments of the next slab from LDS into a second
+//    register set, and runs the MFMAs of the current one between them; one
+//    barrier per slab;
+//  * after the main loop the KS partial sums of a sub-tile meet in LDS by a
+//    reduce-scatter (a fixed tree, deterministic), so each of the waves ends
+//    with a part of the sub-tile and the epilogue uses all of them;
+//  * LoRA: either T = x A^T is accumulated in the main loop
+//    (v_mfma_f32_16x16x32_bf16, the rows of A in the slab next to those of W)
+//    and s T meets B in the epilogue as bf16 hi + lo parts, or (PRE) the hi and
+//    lo parts of s T and the padded rows of B are read from the pre-pass's
+//    workspace.
+// The K order of every output depends on the tile shape alone, and the shape
+// on M, N and K alone, so an output has the same bits whatever the entry point.
+#include "hydra_device.h"
+#include "hydra_internal.h"
+
+namespace hydra {
+namespace {
+
+struct MidArgs {
+  GroupArgs ga;                   // the members' operands; A null: no adapter
+  const uint16_t* ts[kMaxGroup];  // PRE: [M x 2 rp] bf16 hi | lo parts of s x A^T (null: no adapter)
+  const uint16_t* bp[kMaxGroup];  // PRE: [N x rp] bf16
+  int rp;                         // PRE: padded rank
+  int ntm, ntn;                   // tiles of one member
+  int vec4;                       // outputs may be written with 16-byte stores
+};
+
+// s_waitcnt for at most N vector-memory operations and no LDS operation in
+// flight, then the workgroup barrier.
+template <int N>
+__device__ __forceinline__ void mid_barrier() {
+  static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit field");
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (0 << 8) | (((N >> 4) & 3) << 14));
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+constexpr size_t cmax(size_t a, size_t b) { return a > b ? a : b; }
+
+// TM x TN output tile, WM x WN sub-tile per wave, KS waves per sub-tile, BK
+// wide K slabs in a ring of NS stages, RA rows of A in every slab (the padded
+// rank, 0: none).
+template <int TM_, int TN_, int WM_, int WN_, int KS_, int BK_, int NS_, int RA_>
+struct GemmMid {
+  static constexpr int TM = TM_, TN = TN_, WM = WM_, WN = WN_, KS = KS_, BK = BK_, RA = RA_;
+  static constexpr int NWM = TM / WM, NWN = TN / WN, NW = NWM * NWN * KS, NT = NW * 64;
+  static constexpr int MT = WM / 32, NTL = WN / 32, NQ = MT * NTL;
+  static constexpr int CPR = BK / 8;               // 16-byte chunks per LDS row
+  static constexpr int RPB = 64 / CPR;             // rows per copy instruction
+  static constexpr int XB = TM / RPB, WB = TN / RPB, AB = (RA + RPB - 1) / RPB;
+  static constexpr int DPW = (XB + WB + AB + NW - 1) / NW;  // copies per wave per slab
+  static constexpr int ROWS = TM + TN + AB * RPB;
+  static constexpr int PAD = (XB + WB + AB) % NW ? 64 : 0;  // uint4 that the surplus copies fill
+  static constexpr int STAGE = ROWS * CPR;         // uint4 per stage
+  static constexpr int SPW = BK / 16 / KS;         // 16-wide k-steps per wave and slab
+  static constexpr int HS = SPW >= 2 ? SPW / 2 : 1;         // 32-wide k-steps of T per wave and slab
+  static constexpr int TSPLIT = SPW >= 2 ? 1 : 2;           // waves that share one of them
+  static constexpr int TKS = KS / TSPLIT;                   // partial sums of T
+  static constexpr int TPW = RA > 0 ? WM / 16 / NWN / TSPLIT : 1;  // 16-row T tiles per wave
+  static constexpr int BSB = TN * RA * 2, TSB = TM * 2 * RA * 2;   // bytes of B's and s T's LDS copies
+  static constexpr int EXB = KS > 1 ? NW * NQ * 2 * 1024 : 0;      // exchange buffer of the reduce-scatter
+  static constexpr int TRB = RA > 0 ? TKS * TM * RA * 4 : 0;       // partial T
+  static constexpr size_t EPI = BSB + TSB + cmax(EXB, TRB);
+  static constexpr size_t kLds = 160 * 1024;
+  // fewer stages where they do not fit with the rows of A; an even number where
+  // a slab is one k-step (its two fragment sets then alternate with the stages)
+  static constexpr int FIT = int((kLds / 16 - PAD) / STAGE);
+  static constexpr int NS = SPW == 1 ? (FIT < NS_ ? FIT : NS_) & ~1 : FIT < NS_ ? FIT : NS_;
+  static constexpr size_t LDS = cmax((NS * size_t(STAGE) + PAD) * 16, EPI);
+  static constexpr int NU = NQ * 4;                // 4-register units of a sub-tile
+  static_assert(NS >= 2 && (SPW == 1 || SPW % 2 == 0), "ring and k-steps");
+  static_assert(LDS <= kLds, "fits in LDS");
+  static_assert(NU % KS == 0, "the reduce-scatter ends with whole units");
+  static_assert(RA == 0 || TPW * NWN * TSPLIT * 16 == WM, "T rows split over the waves of a row block");
+};
+
+template <int V>
+struct IC {
+  static constexpr int value = V;
+};
+
+template <class G, bool PRE>
+__global__ __launch_bounds__(G::NT, G::NT / 256) void lora_gemm_mid_kernel(MidArgs g) {
+  constexpr int TM = G::TM, TN = G::TN, WM = G::WM, WN = G::WN, KS = G::KS, BK = G::BK, RA = G::RA;
+  constexpr int NW = G::NW, NT = G::NT, MT = G::MT, NTL = G::NTL, NQ = G::NQ, CPR = G::CPR, RPB = G::RPB;
+  constexpr int NS = G::NS, STAGE = G::STAGE, SPW = G::SPW, DPW = G::DPW, NU = G::NU;
+  constexpr int TJ = RA / 16, TJ1 = TJ > 0 ? TJ : 1, TPW = G::TPW, HS = G::HS;
+  constexpr int XROW = 0, WROW = TM, AROW = TM + TN;
+  __shared__ uint4 sm[G::LDS / 16];
+
+  const int M = g.ga.M, N = g.ga.N, K = g.ga.K, r = g.ga.r;
+  const int t = threadIdx.x, lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int kg = wave % KS;            // this wave's share of every slab
+  const int wt = wave / KS;            // sub-tile
+  const int wr = wt / G::NWN, wc = wt % G::NWN;
+  const int l16 = lane & 15, lg = lane >> 4, l32 = lane & 31, lh = lane >> 5;
+
+  // Consecutive workgroups go to consecutive XCDs; each XCD takes a contiguous
+  // range of the logical order, which walks the members and, within one, up to
+  // 8 row tiles per column tile (the tiles that share rows of W run together
+  // on one L2).
+  int gi, tmi, tni;
+  {
+    const int tiles = g.ntm * g.ntn, total = tiles * g.ga.G, bid = blockIdx.x;
+    const int q = total >> 3, rem = total & 7, xcd = bid & 7;
+    int lid = xcd * q + min(xcd, rem) + (bid >> 3);
+    gi = lid / tiles;
+    lid -= gi * tiles;
+    const int per_group = 8 * g.ntn;
+    const int group = lid / per_group, first_m = group * 8, gsize = min(g.ntm - first_m, 8);
+    const int in = lid - group * per_group;
+    tmi = first_m + in % gsize;
+    tni = in / gsize;
+  }
+  gi = __builtin_amdgcn_readfirstlane(gi);
+  const uint16_t* const X = g.ga.x[gi];
+  const uint16_t* const Wt = g.ga.W[gi];
+  const uint16_t* const At = g.ga.A[gi];
+  const uint16_t* const Bt = g.ga.B[gi];
+  float* const y_off = g.ga.y_off[gi];
+  float* const y_on = g.ga.y_on[gi];
+  const int m0 = __builtin_amdgcn_readfirstlane(tmi * TM);
+  const int n0 = __builtin_amdgcn_readfirstlane(tni * TN);
+  const int nkt = (K + BK - 1) / BK;
+  const bool lora = y_on != nullptr && (PRE ? g.ts[gi] != nullptr : RA > 0 && At != nullptr && Bt != nullptr);
+
+  // LDS chunk index of (row, 16-byte chunk c): the chunk is XOR-ed with bits of
+  // the row so that the 16 lanes of a read phase (16 consecutive rows, one
+  // chunk) cover all banks once.
+  auto swz = [](int row) __attribute__((always_inline)) { return CPR == 8 ? (row >> 1) & 7 : row & 15; };
+  static_assert(CPR == 8 || CPR == 16, "rows of 128 or 256 bytes");
+  auto lds_idx = [&](int row, int c) __attribute__((always_inline)) { return row * CPR + (c ^ swz(row)); };
+
+  // ---- copies: one instruction moves RPB rows x BK values (64 lanes x 16
+  // bytes); the slab's row blocks (x, W, A) are dealt round-robin to the waves.
+  // Every wave issues DPW copies (surplus ones write zeros past the stages), so
+  // that the waits below count the same in every wave.
+  static_assert(G::XB % NW == 0 && G::WB % NW == 0, "copy j of every wave is of one operand");
+  constexpr int XJ = G::XB / NW, WJ = G::WB / NW;
+  const int rl = lane / CPR, pc = lane % CPR;
+  const int row_bytes = K * 2;
+  const i32x4_t xr = make_rsrc_raw(X + (size_t)m0 * K, (uint32_t)min(TM, M - m0) * K * 2u);
+  const i32x4_t wrs = make_rsrc_raw(Wt + (size_t)n0 * K, (uint32_t)min(TN, N - n0) * K * 2u);
+  const bool t_on = RA > 0 && lora;
+  const i32x4_t ars = make_rsrc_raw(t_on ? At : nullptr, t_on ? (uint32_t)min(r, RA) * K * 2u : 0u);
+  auto dma = [&](int stage, int kt, int j) __attribute__((always_inline)) {
+    const bool is_a = j >= XJ + WJ;
+    const int b = wave + (j < XJ ? j : j < XJ + WJ ? j - XJ : j - XJ - WJ) * NW;  // row block of its operand
+    const int lrow = (j < XJ ? XROW : j < XJ + WJ ? WROW : AROW) + b * RPB;       // its first LDS row
+    const bool real = !is_a || b < G::AB;
+    const int c = pc ^ swz(lrow + rl);
+    const int k = kt * BK + c * 8;
+    dma16(j < XJ ? xr : j < XJ + WJ ? wrs : ars, real ? sm + stage * STAGE + lrow * CPR : sm + NS * STAGE,
+          real && k < K ? (b * RPB + rl) * row_bytes + k * 2 : kOutOfRange);
+  };
+
+  f32x16_t acc[MT][NTL];
+  f32x4_t accT[TPW][TJ1];
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int j = 0; j < NTL; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+#pragma unroll
+  for (int q = 0; q < TPW; ++q)
+#pragma unroll
+    for (int j = 0; j < TJ1; ++j) accT[q][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+  // Fragments of one 16-wide k-step (W rows as the A operand, x rows as the B
+  // operand), double buffered across the wave's k-steps, and of T: this wave's
+  // x rows and the rows of A for its 32-wide part of a slab (16x16x32 layout),
+  // read and used a slab ahead.
+  struct Frag {
+    uint4 w[NTL], x[MT];
+  };
+  constexpr int NRM = NTL + MT, NRT = TJ > 0 ? HS * (TPW + TJ) : 0;
+  Frag F[2];
+  uint4 tx[HS][TPW], ta[HS][TJ1];
+  const int trow = wr * WM + (G::TSPLIT == 1 ? wc : (kg & 1) * G::NWN + wc) * TPW * 16;  // first T row of this wave
+  const int tchunk = (G::TSPLIT == 1 ? kg * HS : kg >> 1) * 4 + lg;
+  auto read_main = [&](Frag& f, int stage, int st, int q) __attribute__((always_inline)) {
+    const uint4* s = sm + stage * STAGE;
+    const int ch = 2 * (kg * SPW + st) + lh;
+    if (q < NTL)
+      f.w[q] = s[lds_idx(WROW + wc * WN + q * 32 + l32, ch)];
+    else
+      f.x[q - NTL] = s[lds_idx(XROW + wr * WM + (q - NTL) * 32 + l32, ch)];
+  };
+  auto read_t = [&](int stage, int r) __attribute__((always_inline)) {
+    const uint4* s = sm + stage * STAGE;
+    const int hs = r / (TPW + TJ1), q = r % (TPW + TJ1);
+    const int ch = tchunk + 4 * hs;
+    if (q < TPW)
+      tx[hs][q] = s[lds_idx(XROW + trow + q * 16 + l16, ch)];
+    else
+      ta[hs][q - TPW] = s[lds_idx(AROW + (q - TPW) * 16 + l16, ch)];
+  };
+  auto mfma_t = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int hs = 0; hs < HS; ++hs)
+#pragma unroll
+      for (int q = 0; q < TPW; ++q)
+#pragma unroll
+        for (int j = 0; j < TJ; ++j) accT[q][j] = mfma16(tx[hs][q], ta[hs][j], accT[q][j]);
+  };
+  // k-step S of slab kt in stage ST: the MFMAs of its fragments, between them
+  // the reads of the next k-step; the slab's last k-step comes after the
+  // barrier and also copies slab kt + NS into this stage and takes T of slab
+  // kt + 1.
+  auto kstep = [&](auto S, auto ST, auto PAR, int kt) __attribute__((always_inline)) {
+    constexpr int sp = decltype(S)::value, st = decltype(ST)::value, par = decltype(PAR)::value;
+    constexpr bool last = sp == SPW - 1;
+    constexpr int rst = last ? (st + 1) % NS : st, rsp = last ? 0 : sp + 1;
+    if constexpr (last) mid_barrier<(NS - 2) * DPW>();  // slab kt + 1 has landed, slab kt is in registers everywhere
+    const Frag& fc = F[par];
+    Frag& fn = F[par ^ 1];
+    constexpr int NR = NRM + (last ? NRT : 0), ND = last ? DPW : 0;
+#pragma unroll
+    for (int m = 0; m < NQ; ++m) {
+      acc[m / NTL][m % NTL] = mfma32(fc.w[m % NTL], fc.x[m / NTL], acc[m / NTL][m % NTL]);
+#pragma unroll
+      for (int r = m * NR / NQ; r < (m + 1) * NR / NQ; ++r) {
+        if (r < NRM)
+          read_main(fn, rst, rsp, r);
+        else
+          read_t(rst, r - NRM);
+      }
+#pragma unroll
+      for (int j = m * ND / NQ; j < (m + 1) * ND / NQ; ++j) dma(st, kt + NS, j);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if constexpr (last && TJ > 0) mfma_t();
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto slab = [&](auto ST, auto PAR, int kt) __attribute__((always_inline)) {
+    constexpr int par = decltype(PAR)::value;
+    kstep(IC<0>{}, ST, IC<par>{}, kt);
+    if constexpr (SPW > 1) kstep(IC<(SPW > 1 ? 1 : 0)>{}, ST, IC<par ^ 1>{}, kt);
+    if constexpr (SPW > 2) {
+      kstep(IC<(SPW > 2 ? 2 : 0)>{}, ST, IC<par>{}, kt);
+      kstep(IC<(SPW > 2 ? 3 : 0)>{}, ST, IC<par ^ 1>{}, kt);
+    }
+  };
+
+  // B's rows of this tile, zero padded to RA, requested first and put in LDS
+  // after the main loop (2-byte loads: B has rows of r values at any even address).
+  constexpr int BPT = RA > 0 ? (TN * RA + NT - 1) / NT : 1;
+  uint32_t bv[BPT];
+  if constexpr (RA > 0) {
+    const __amdgpu_buffer_rsrc_t brs =
+        make_rsrc(lora ? Bt + (size_t)n0 * r : nullptr, lora ? (uint32_t)min(TN, N - n0) * r * 2u : 0u);
+#pragma unroll
+    for (int i = 0; i < BPT; ++i) {
+      const int e = t + i * NT, n = e / RA, j = e % RA;
+      bv[i] = __builtin_amdgcn_raw_buffer_load_b16(brs, e < TN * RA && j < r ? (n * r + j) * 2 : kOutOfRange, 0, 0);
+    }
+  }
+
+  // prologue: slabs 0 .. NS - 1 (those past the last read zeros)
+#pragma unroll
+  for (int s = 0; s < NS; ++s)
+#pragma unroll
+    for (int j = 0; j < DPW; ++j) dma(s, s, j);
+  mid_barrier<(NS - 1) * DPW>();
+#pragma unroll
+  for (int r = 0; r < NRM; ++r) read_main(F[0], 0, 0, r);
+  if constexpr (TJ > 0) {
+#pragma unroll
+    for (int r = 0; r < NRT; ++r) read_t(0, r);
+    mfma_t();
+  }
+  // the slabs, unrolled over the ring 
+  constexpr int PS = SPW == 1 ? 1 : 0;
+  constexpr int UN = NS;
+  static_assert(UN <= 8, "slabs listed below");
+  for (int kt = 0; kt < nkt; kt += UN) {
+#define HYDRA_MID_SLAB(u)                 \
+  if constexpr ((u) < UN)                 \
+    if ((u) == 0 || kt + (u) < nkt) slab(IC<(u) % NS>{}, IC<((u) & PS)>{}, kt + (u));
+    HYDRA_MID_SLAB(0)
+    HYDRA_MID_SLAB(1)
+    HYDRA_MID_SLAB(2)
+    HYDRA_MID_SLAB(3)
+    HYDRA_MID_SLAB(4)
+    HYDRA_MID_SLAB(5)
+    HYDRA_MID_SLAB(6)
+    HYDRA_MID_SLAB(7)
+#undef HYDRA_MID_SLAB
+  }
+  mid_barrier<0>();  // every copy has landed, every wave is done with the ring
+
+  // ---------------------------------------------------------------- epilogue
+  char* const lds = reinterpret_cast<char*>(sm);
+  uint16_t* const Bs = reinterpret_cast<uint16_t*>(lds);
+  uint16_t* const Ts = reinterpret_cast<uint16_t*>(lds + G::BSB);
+  char* const scratch = lds + G::BSB + G::TSB;
+  if constexpr (RA > 0) {
+#pragma unroll
+    for (int i = 0; i < BPT; ++i)
+      if (t + i * NT < TN * RA) Bs[t + i * NT] = (uint16_t)bv[i];
+    // accT[q][j] holds T[trow + 16 q + 4 lg + e][16 j + l16] over this wave's k values
+    float* tp = reinterpret_cast<float*>(scratch);
+#pragma unroll
+    for (int q = 0; q < TPW; ++q)
+#pragma unroll
+      for (int j = 0; j < TJ; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          tp[((kg / G::TSPLIT) * TM + trow + q * 16 + 4 * lg + e) * RA + 16 * j + l16] = accT[q][j][e];
+    __syncthreads();
+    for (int e = t; e < TM * RA; e += NT) {
+      float v = tp[e];
+#pragma unroll
+      for (int k2 = 1; k2 < G::TKS; ++k2) v += tp[k2 * TM * RA + e];
+      v *= g.ga.s[gi];
+      const uint32_t hi = f32_to_bf16_rne(v);
+      const uint32_t lo = f32_to_bf16_rne(v - bf16_to_f32(hi));
+      const int row = e / RA, j = e % RA;
+      Ts[row * 2 * RA + j] = (uint16_t)hi;
+      Ts[row * 2 * RA + RA + j] = (uint16_t)lo;
+    }
+    __syncthreads();
+  }
+
+  // Reduce-scatter of the KS partial sub-tiles over units of four registers
+  // (unit u = 4 (mi NTL + ni) + i): at step 2^b the waves kg and kg ^ 2^b
+  // exchange halves of the units they still hold.  Afterwards this wave holds
+  // the NU / KS units from u0.
+  f32x4_t un[NU];
+#pragma unroll
+  for (int q = 0; q < NQ; ++q)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      un[q * 4 + i] = f32x4_t{acc[q / NTL][q % NTL][4 * i], acc[q / NTL][q % NTL][4 * i + 1],
+                              acc[q / NTL][q % NTL][4 * i + 2], acc[q / NTL][q % NTL][4 * i + 3]};
+  int u0 = 0;
+  if constexpr (KS > 1) {
+    f32x4_t* ex = reinterpret_cast<f32x4_t*>(scratch);
+    constexpr int HALF = NU / 2;
+    auto step = [&](auto BIT, auto CNT) __attribute__((always_inline)) {
+      constexpr int bit = decltype(BIT)::value, cnt = decltype(CNT)::value;
+      const bool up = (kg & bit) != 0;  // wave-uniform: this wave keeps the upper half
+      if constexpr (bit > 1) __syncthreads();  // the previous step's values have been read
+#pragma unroll
+      for (int u = 0; u < cnt; ++u) {
+        ex[(wave * HALF + u) * 64 + lane] = up ? un[u] : un[u + cnt];
+        un[u] = up ? un[u + cnt] : un[u];
+      }
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < cnt; ++u) un[u] += ex[((wave ^ bit) * HALF + u) * 64 + lane];
+      u0 += up ? cnt : 0;
+    };
+    step(IC<1>{}, IC<NU / 2>{});
+    if constexpr (KS > 2) step(IC<2>{}, IC<NU / 4>{});
+    if constexpr (KS > 4) step(IC<4>{}, IC<NU / 8>{});
+    static_assert(KS <= 8, "steps listed above");
+  }
+  constexpr int MYU = NU / KS;             // units held
+  constexpr int MYQ = MYU >= 4 ? MYU / 4 : 1;  // sub-tile blocks they lie in
+  constexpr int UPQ = MYU / MYQ;           // units per block
+  u0 = __builtin_amdgcn_readfirstlane(u0);
+  auto finish = [&](auto BI) __attribute__((always_inline)) {
+    constexpr int b = decltype(BI)::value;
+    const int q = (u0 >> 2) + b, i0 = MYU >= 4 ? 0 : (u0 & 3);  // (wave-uniform)
+    const int mi = q / NTL, ni = q % NTL;
+    const int row = m0 + wr * WM + mi * 32 + l32;
+    const int colb = n0 + wc * WN + ni * 32 + 4 * lh;
+    auto store = [&](float* y, const f32x4_t (&v)[UPQ]) __attribute__((always_inline)) {
+      if (row >= M) return;
+      float* yr = y + (size_t)row * N;
+#pragma unroll
+      for (int k = 0; k < UPQ; ++k) {
+        const int col = colb + 8 * (i0 + k);
+        if (g.vec4 && col + 3 < N) {
+          *reinterpret_cast<f32x4_t*>(yr + col) = v[k];
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (col + e < N) yr[col + e] = v[k][e];
+        }
+      }
+    };
+    f32x4_t v[UPQ];
+#pragma unroll
+    for (int k = 0; k < UPQ; ++k) v[k] = un[b * UPQ + k];
+    if (y_off) store(y_off, v);
+    if (!y_on) return;
+    if (lora) {
+      // s T B^T of the whole 32 x 32 block; this wave adds the units it holds.
+      // A operand: rows of [B | B], B operand: rows of [hi | lo] of s T.
+      f32x16_t L;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) L[e] = 0.f;
+      if constexpr (PRE) {
+        const int rp = g.rp;
+        const int mr = __builtin_amdgcn_readfirstlane(m0 + wr * WM + mi * 32);
+        const int nr = __builtin_amdgcn_readfirstlane(n0 + wc * WN + ni * 32);
+        const __amdgpu_buffer_rsrc_t tr =
+            make_rsrc(g.ts[gi] + (size_t)min(mr, M) * 2 * rp, (uint32_t)max(0, min(32, M - mr)) * 4u * rp);
+        const __amdgpu_buffer_rsrc_t br =
+            make_rsrc(g.bp[gi] + (size_t)min(nr, N) * rp, (uint32_t)max(0, min(32, N - nr)) * 2u * rp);
+        for (int k0 = 0; k0 < 2 * rp; k0 += 64) {
+          uint4 tf[4], bf[4];
+#pragma unroll
+          for (int ks = 0; ks < 4; ++ks) {
+            const int k = k0 + ks * 16 + lh * 8;
+            tf[ks] = buf_load16(tr, k < 2 * rp ? (l32 * 2 * rp + k) * 2 : kOutOfRange);
+            bf[ks] = buf_load16(br, k < 2 * rp ? (l32 * rp + (k & (rp - 1))) * 2 : kOutOfRange);
+          }
+#pragma unroll
+          for (int ks = 0; ks < 4; ++ks) L = mfma32(bf[ks], tf[ks], L);
+        }
+      } else {
+        constexpr int RA1 = RA > 0 ? RA : 1;
+#pragma unroll
+        for (int ks = 0; ks < 2 * RA / 16; ++ks) {
+          const int k = ks * 16 + lh * 8;
+          const uint4 bf = *reinterpret_cast<const uint4*>(Bs + (wc * WN + ni * 32 + l32) * RA + k % RA1);
+          const uint4 tf = *reinterpret_cast<const uint4*>(Ts + (wr * WM + mi * 32 + l32) * 2 * RA + k);
+          L = mfma32(bf, tf, L);
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < UPQ; ++k) {
+        f32x4_t l;
+        if constexpr (MYU >= 4) {
+          l = f32x4_t{L[4 * k], L[4 * k + 1], L[4 * k + 2], L[4 * k + 3]};
+        } else {
+          l = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (i == i0 + k) l = f32x4_t{L[4 * i], L[4 * i + 1], L[4 * i + 2], L[4 * i + 3]};
+        }
+        v[k] += l;
+      }
+    }
+    store(y_on, v);
+  };
+  static_assert(MYQ <= 4 && UPQ * MYQ == MYU && (MYU >= 4 || 4 % MYU == 0), "blocks listed below");
+  finish(IC<0>{});
+  if constexpr (MYQ > 1) finish(IC<1>{});
+  if constexpr (MYQ > 2) finish(IC<2>{});
+  if constexpr (MYQ > 3) finish(IC<3>{});
+}
+
+// The tiles, smallest first, with the model that chooses among them (us, at the
+// end of a tile's last round): base + rounds x (fixed + slabs x step), rounds
+// of 256 tiles (one workgroup per CU) and slabs of 64 k values.  The numbers
+// are fits to kernel times over M = 17 ... 4096 and eight (K, N) from 700 to
+// 11008 at rank 16 (rms error 11-18%; the model's choice is 0.4% slower than
+// the best one on average, 16% at most, and never slower than the 128 x 256
+// tile by more than 1.2%).  What they say: a 64-wide slab of a tile costs its
+// bytes at 45 B/clk for the smallest tiles to 60 B/clk for the largest, so a
+// larger tile is cheaper per output as long as it still gives 256 tiles.
+// M x K x N, us: 48 x 4096 x 4096 41.4 -> 11.6, 333 x 4096 x 11008 72 -> 58,
+// 512 x 4096 x 4096 47.6 -> 29.9, 1000 x 11008 x 4096 157 -> 121, 500 x 2048 x
+// 2048 30.2 -> 13.6 (128 x 256 tile -> here, rank 16).
+struct MidTile {
+  int tm, tn;
+  float base, fixed, step;
+};
+constexpr MidTile kMidTiles[] = {{32, 32, 1.7f, 2.3f, 0.123f},   {32, 64, 1.5f, 3.0f, 0.176f},
+                                 {64, 64, 0.9f, 4.2f, 0.221f},   {64, 128, 0.f, 6.1f, 0.354f},
+                                 {128, 128, 0.f, 6.6f, 0.482f},  {128, 192, 0.f, 8.4f, 0.613f}};
+constexpr MidTile kBigTile = {kGemmTileM, kGemmTileN, 0.f, 9.0f, 0.720f};  // lora_gemm_kernel
+constexpr int kMidTileCount = sizeof(kMidTiles) / sizeof(kMidTiles[0]);
+
+float tile_cost(const MidTile& c, int M, int N, int K) {
+  const int64_t tiles = (int64_t)((M + c.tm - 1) / c.tm) * ((N + c.tn - 1) / c.tn);
+  return c.base + (float)((tiles + 255) / 256) * (c.fixed + (float)((K + 63) / 64) * c.step);
+}
+
+template <class G, bool PRE>
+void launch_tile(MidArgs& g, hipStream_t stream) {
+  g.ntm = (g.ga.M + G::TM - 1) / G::TM;
+  g.ntn = (g.ga.N + G::TN - 1) / G::TN;
+  hipLaunchKernelGGL((lora_gemm_mid_kernel<G, PRE>), dim3(g.ntm * g.ntn * g.ga.G), dim3(G::NT), 0, stream, g);
+}
+
+template <int TM, int TN, int WM, int WN, int KS, int BK, int NS>
+hipError_t launch_mid(MidArgs& g, int ra, hipStream_t stream) {
+  if (g.rp > 0)
+    launch_tile<GemmMid<TM, TN, WM, WN, KS, BK, NS, 0>, true>(g, stream);
+  else if (ra == 0)
+    launch_tile<GemmMid<TM, TN, WM, WN, KS, BK, NS, 0>, false>(g, stream);
+  else if (ra == 16)
+    launch_tile<GemmMid<TM, TN, WM, WN, KS, BK, NS, 16>, false>(g, stream);
+  else if (ra == 32)
+    launch_tile<GemmMid<TM, TN, WM, WN, KS, BK, NS, 32>, false>(g, stream);
+  else if (ra == 64)
+    launch_tile<GemmMid<TM, TN, WM, WN, KS, BK, NS, 64>, false>(g, stream);
+  else
+    return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+
+}  // namespace
+
+int gemm_mid_tile(int M, int N, int K) {
+  int best = -1;
+  float cost = tile_cost(kBigTile, M, N, K);
+  for (int i = 0; i < kMidTileCount; ++i) {
+    const float c = tile_cost(kMidTiles[i], M, N, K);
+    if (c < cost) {
+      cost = c;
+      best = i;
+    }
+  }
+  return best;
+}
+
+hipError_t launch_lora_gemm_mid(const GroupArgs& ga, const uint16_t* const* ts, const uint16_t* const* bp, int rp_pre,
+                                int tile, hipStream_t stream) {
+  MidArgs g{};
+  g.ga = ga;
+  g.rp = rp_pre;
+  g.vec4 = ga.N % 4 == 0;
+  bool any_on = false;
+  for (int i = 0; i < ga.G; ++i) {
+    g.ts[i] = ts ? ts[i] : nullptr;
+    g.bp[i] = bp ? bp[i] : nullptr;
+    g.vec4 = g.vec4 && (reinterpret_cast<uintptr_t>(ga.y_off[i]) & 15) == 0 &&
+             (reinterpret_cast<uintptr_t>(ga.y_on[i]) & 15) == 0;
+    any_on = any_on || (ga.y_on[i] && ga.A[i] && ga.B[i]);
+  }
+  const int ra = any_on ? padded_rank(ga.r) : 0;
+  switch (tile) {
+    case 0: return launch_mid<32, 32, 32, 32, 4, 128, 5>(g, ra, stream);
+    case 1: return launch_mid<32, 64, 32, 64, 4, 128, 5>(g, ra, stream);
+    case 2: return launch_mid<64, 64, 32, 64, 4, 128, 4>(g, ra, stream);
+    case 3: return launch_mid<64, 128, 64, 64, 4, 64, 6>(g, ra, stream);
+    case 4: return launch_mid<128, 128, 64, 64, 2, 64, 5>(g, ra, stream);
+    case 5: return launch_mid<128, 192, 64, 96, 2, 64, 4>(g, ra, stream);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+}  // namespace hydra

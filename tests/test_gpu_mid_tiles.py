@@ -1,0 +1,97 @@
+"""The dual GEMM's smaller tiles (17 rows to a few hundred): edges of every tile, K shorter than a slab and longer than
+the ring, every way the LoRA update reaches them, against the float64 oracle; and the bits that the entry points share.
+Tolerances: the arithmetic bound of the other linear tests (2e-4 relative)."""
+import numpy as np
+import pytest
+
+import paper_2309_00754_amd as H
+import workloads as WL
+from oracle import lora_linear_ref
+from gpu_helpers import assert_rel, dev_bf16, host, say
+
+pytestmark = pytest.mark.gpu
+
+# (M, N, K) by the tile that the size model picks: one with remainders in both directions, one of whole tiles
+SHAPES = [
+    (17, 33, 8), (31, 700, 72), (64, 96, 1536),               # 32 x 32
+    (65, 5000, 264), (96, 4096, 128),                         # 32 x 64
+    (40, 8200, 136), (128, 8192, 1032),                       # 64 x 64
+    (200, 5000, 264), (300, 5001, 1000), (128, 16384, 128),   # 64 x 128
+    (230, 11000, 520), (256, 8192, 2048),                     # 128 x 128
+    (129, 16500, 72), (400, 11001, 520), (384, 12288, 256),   # 128 x 192
+]
+
+
+def _inputs(M, N, K, r, dev):
+    c = WL.gen_linear(9000 + M + 3 * N + 7 * K + r, M, K, N, r)
+    x, W = dev_bf16(c.x, dev), dev_bf16(c.W, dev)
+    return c, x, W, dev_bf16(c.A, dev) if r else None, dev_bf16(c.B, dev) if r else None
+
+
+def _nan(M, N, dev):
+    import torch
+    return torch.full((M, N), float("nan"), device=dev)
+
+
+@pytest.mark.parametrize("r", [0, 8, 16, 20, 64, 100])
+@pytest.mark.parametrize("M,N,K", SHAPES)
+def test_mid_tiles(M, N, K, r, dev):
+    import torch
+    say("mid tile", M, N, K, r)
+    c, x, W, A, B = _inputs(M, N, K, r, dev)
+    e_off, e_on = lora_linear_ref(c.x, c.W, c.A, c.B, c.s)
+    w_off, w_on = _nan(M, N, dev), _nan(M, N, dev)
+    H.hydra_lora_linear_ws(x, W, A, B, c.s, w_off, w_on)
+    torch.cuda.synchronize()
+    assert_rel(host(w_off), e_off, "ws y_off")
+    assert_rel(host(w_on), e_on, "ws y_on")
+    if r > 64:
+        return
+    y_off, y_on = _nan(M, N, dev), _nan(M, N, dev)
+    H.hydra_lora_linear(x, W, A, B, c.s, y_off, y_on)
+    only = _nan(M, N, dev)
+    H.hydra_lora_linear(x, W, A, B, c.s, None, only)
+    torch.cuda.synchronize()
+    assert_rel(host(y_off), e_off, "y_off")
+    assert_rel(host(y_on), e_on, "y_on")
+    assert torch.equal(y_off, w_off) and torch.equal(only, y_on)
+    if r:  # a zero scale and a zero B add exact zeros
+        H.hydra_lora_linear(x, W, A, B, 0.0, y_off, y_on)
+        H.hydra_lora_linear(x, W, A, torch.zeros_like(B), c.s, w_off, w_on)
+        torch.cuda.synchronize()
+        assert torch.equal(y_on, y_off) and torch.equal(w_on, w_off)
+
+
+@pytest.mark.parametrize("M,N,K,r", [(33, 700, 264, 16), (40, 1500, 136, 64), (100, 999, 520, 128), (65, 2052, 264, 128),
+                                     (200, 3001, 72, 8)])
+def test_mid_group_members_have_the_bits_of_single_calls(M, N, K, r, dev):
+    """Members with, without and with only one of the outputs of an adapter, in one launch."""
+    import torch
+    say("mid group", M, N, K, r)
+    G = 4
+    ms = [_inputs(M, N, K + 0 * i, r, dev) for i in range(G)]
+    xs, Ws = [m[1] for m in ms], [torch.roll(m[2], i, 0) for i, m in enumerate(ms)]
+    As, Bs = [m[3] for m in ms], [m[4] for m in ms]
+    ss = [2.0, -0.5, 1.0, 3.0]
+    offs = [_nan(M, N, dev), None, _nan(M, N, dev), _nan(M, N, dev)]
+    ons = [_nan(M, N, dev), _nan(M, N, dev), None, _nan(M, N, dev)]
+    if r > 64:
+        ws = H.hydra_lora_linear_group_workspace(G, M, N, r, dev)
+        H.hydra_lora_linear_group_ws(xs, Ws, As, Bs, ss, offs, ons, ws)
+    else:
+        H.hydra_lora_linear_group(xs, Ws, As, Bs, ss, offs, ons)
+    torch.cuda.synchronize()
+    for i in range(G):
+        off, on = _nan(M, N, dev), _nan(M, N, dev)
+        (H.hydra_lora_linear_ws if r > 64 else H.hydra_lora_linear)(xs[i], Ws[i], As[i], Bs[i], ss[i], off, on)
+        torch.cuda.synchronize()
+        assert offs[i] is None or torch.equal(offs[i], off)
+        assert ons[i] is None or torch.equal(ons[i], on)
+    # a group without any adapter
+    offs = [_nan(M, N, dev) for _ in range(G)]
+    ons = [_nan(M, N, dev) for _ in range(G)]
+    H.hydra_lora_linear_group(xs, Ws, [None] * G, [None] * G, ss, offs, ons)
+    torch.cuda.synchronize()
+    for i in range(G):
+        assert torch.equal(offs[i], ons[i])
+        assert np.isfinite(host(offs[i])).all()
