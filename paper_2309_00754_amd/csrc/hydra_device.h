@@ -95,13 +95,16 @@ __device__ __forceinline__ float log_e(float x) { return __builtin_amdgcn_logf(x
 // sum are rounded separately (no contraction), so merge(a, b) == merge(b, a)
 // bit for bit.  An empty side has m = -inf and s = 0.
 __device__ __forceinline__ void lse_merge(float& m, float& s, float m2, float s2) {
+#pragma clang fp contract(off)
   const float mn = fmaxf(m, m2);
   if (mn == -INFINITY) {
     m = mn;
     s = 0.f;
     return;
   }
-  s = __fadd_rn(__fmul_rn(s, exp_e(m - mn)), __fmul_rn(s2, exp_e(m2 - mn)));
+  const float a = s * __builtin_amdgcn_exp2f((m - mn) * kLog2e);
+  const float b = s2 * __builtin_amdgcn_exp2f((m2 - mn) * kLog2e);
+  s = a + b;
   m = mn;
 }
 

@@ -76,6 +76,7 @@ struct TpreArgs {
   float* part;        // [kTpreMaxChunks x M x RP] fp32 partial sums over K chunks
   uint16_t* tT;       // [2][RP][Mp] bf16 hi and lo planes of (s T)^T, rows M..Mp zero, or nullptr
   int Mp;             // leading dimension of tT (M rounded up to 32)
+  int Kform;          // the K that the choice of kernel looks at (0: K; jobs that may or may not run together share it)
 };
 // K is split into at most kTpreMaxChunks chunks of at least 1024, so that
 // the pre-pass spreads over many workgroups; the partial products are then
@@ -112,6 +113,7 @@ struct ScoreGemmArgs {
   uint16_t* bp_buf;        // room for the padded copy
   float* tpart;            // LoRA pre-pass partial sums over K chunks
   int ntn;                 // number of column tiles
+  int rp;                  // padded rank (set by the launcher)
   int ntm;                 // number of row tiles (set by the launcher)
   // Two inputs (the actor pass and the LoRA-off pass have their own hidden
   // states): lin.x holds the LoRA-off rows, x_act the rows scored with the
@@ -229,6 +231,10 @@ int gemm_mid_tile(int M, int N, int K);
 // adapter); without, from A and B (padded rank up to 64).
 hipError_t launch_lora_gemm_mid(const GroupArgs& ga, const uint16_t* const* ts, const uint16_t* const* bp, int rp_pre,
                                 int tile, hipStream_t stream);
+// Partial T over K chunks of the pre-pass jobs (same M; padded rank 64 or 128)
+// on those tiles, one launch; nkc[j] receives the number of chunks written to
+// as[j].part, which depends on M, K and rp alone.
+hipError_t launch_t_part_mid(const TpreArgs* as, int n, int rp, int* nkc, hipStream_t stream);
 hipError_t launch_lora_gemm(const LinearArgs& a, hipStream_t stream);
 // The same with the LoRA update from the pre-pass: ts [M x 2 RP] and bp [N x RP]
 // bf16 workspace (RP = padded rank of a.r, up to 128).

@@ -1,0 +1,52 @@
+"""The scoring GEMM's three row tiles (64, 128 and 256 rows): their edges against the float64 oracle, and equal bits where
+the one-input and the two-input pass of the same rows run on different tiles."""
+import pytest
+
+import paper_2309_00754_amd as H
+import workloads as WL
+from oracle import score_head_ref
+from gpu_helpers import assert_abs, assert_rel, dev_bf16, host, say
+
+pytestmark = pytest.mark.gpu
+
+KEYS = ("lp_on", "lp_off", "kl", "lse_on", "lse_off")
+
+
+def _score(s, dev, two):
+    import torch
+    A, B = (dev_bf16(s.A, dev), dev_bf16(s.B, dev)) if s.r else (None, None)
+    h, W = dev_bf16(s.h, dev), dev_bf16(s.W_lm, dev)
+    out = {k: torch.full((s.M,), float("nan"), device=dev) for k in KEYS}
+    reward = torch.full((s.n_seq,), float("nan"), device=dev)
+    args = (W, A, B, s.s, torch.from_numpy(s.ids).to(dev), dev_bf16(s.w_rm, dev), s.n_seq, s.seq_len, out["lp_on"],
+            out["lp_off"], out["kl"])
+    kw = dict(reward=reward, lse_on=out["lse_on"], lse_off=out["lse_off"])
+    if two:
+        H.hydra_score_two_input(h, h, *args, **kw)
+    else:
+        H.hydra_score(h, *args, **kw)
+    torch.cuda.synchronize()
+    return out, reward
+
+
+# rows, K and V by the tile that the size model picks (one input); K of 8: shorter than a slab; 200: a remainder of
+# both slab widths; r of 16 fills half a 64-wide LoRA slab
+@pytest.mark.parametrize("n_seq,seq_len,K,V,r", [
+    (1, 1, 8, 1, 0), (1, 63, 200, 257, 16), (2, 65, 64, 512, 128), (3, 43, 1032, 3000, 8),    # 64 rows
+    (1, 100, 200, 33000, 16), (2, 64, 512, 33001, 64), (1, 130, 72, 22016, 100),              # 128 rows
+    (1, 200, 72, 50000, 16), (1, 257, 136, 30000, 0), (4, 128, 392, 12345, 128),              # 256 rows
+])
+def test_score_tiles(n_seq, seq_len, K, V, r, dev):
+    import torch
+    say("score tile", n_seq, seq_len, K, V, r)
+    s = WL.gen_score_head(8100 + n_seq * seq_len + K + V + r, n_seq, seq_len, K, V, r)
+    one, rew1 = _score(s, dev, False)
+    two, rew2 = _score(s, dev, True)
+    e = score_head_ref(s.h, s.W_lm, s.A, s.B, s.s, s.ids, s.w_rm, s.n_seq, s.seq_len)
+    for k in KEYS:
+        assert_abs(host(one[k]), e[k], k)
+        assert torch.equal(one[k], two[k]), k
+    assert_rel(host(rew1), e["reward"], "reward")
+    assert torch.equal(rew1, rew2)
+    if r == 0:
+        assert torch.equal(one["lp_on"], one["lp_off"])
