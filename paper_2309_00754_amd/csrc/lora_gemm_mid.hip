@@ -34,6 +34,9 @@ struct MidArgs {
   const uint16_t* ts[kMaxGroup];  // PRE: [M x 2 rp] bf16 hi | lo parts of s x A^T (null: no adapter)
   const uint16_t* bp[kMaxGroup];  // PRE: [N x rp] bf16
   int rp;                         // PRE: padded rank
+  int kall[kMaxGroup];            // PART: K of member i, cut into nkc[i] chunks of kch[i] (ga.K unused)
+  int kch[kMaxGroup];
+  int nkc[kMaxGroup];
   int ntm, ntn;                   // tiles of one member
   int vec4;                       // outputs may be written with 16-byte stores
 };
@@ -93,7 +96,13 @@ struct IC {
   static constexpr int value = V;
 };
 
-template <class G, bool PRE>
+// PLAIN: T in the tile (or no adapter); PRE: the update from the pre-pass;
+// PART: the pre-pass's own product T = x A^T, one K chunk per workgroup: W is
+// A ([r x K], rows past r read as zeros), N the padded rank and y_off the
+// partial sums [chunk][M][N].
+enum MidMode { PLAIN, PRE, PART };
+
+template <class G, MidMode MODE>
 __global__ __launch_bounds__(G::NT, G::NT / 256) void lora_gemm_mid_kernel(MidArgs g) {
   constexpr int TM = G::TM, TN = G::TN, WM = G::WM, WN = G::WN, KS = G::KS, BK = G::BK, RA = G::RA;
   constexpr int NW = G::NW, NT = G::NT, MT = G::MT, NTL = G::NTL, NQ = G::NQ, CPR = G::CPR, RPB = G::RPB;
@@ -102,7 +111,7 @@ __global__ __launch_bounds__(G::NT, G::NT / 256) void lora_gemm_mid_kernel(MidAr
   constexpr int XROW = 0, WROW = TM, AROW = TM + TN;
   __shared__ uint4 sm[G::LDS / 16];
 
-  const int M = g.ga.M, N = g.ga.N, K = g.ga.K, r = g.ga.r;
+  const int M = g.ga.M, N = g.ga.N, r = g.ga.r;
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int kg = wave % KS;            // this wave's share of every slab
@@ -114,13 +123,18 @@ __global__ __launch_bounds__(G::NT, G::NT / 256) void lora_gemm_mid_kernel(MidAr
   // range of the logical order, which walks the members and, within one, up to
   // 8 row tiles per column tile (the tiles that share rows of W run together
   // on one L2).
-  int gi, tmi, tni;
+  int gi, tmi, tni, kc = 0;
   {
-    const int tiles = g.ntm * g.ntn, total = tiles * g.ga.G, bid = blockIdx.x;
+    const int tiles = g.ntm * g.ntn, total = gridDim.x, bid = blockIdx.x;
     const int q = total >> 3, rem = total & 7, xcd = bid & 7;
     int lid = xcd * q + min(xcd, rem) + (bid >> 3);
     gi = lid / tiles;
     lid -= gi * tiles;
+    if constexpr (MODE == PART) {  // gi counts (member, chunk) pairs
+      kc = gi;
+      gi = 0;
+      while (kc >= g.nkc[gi]) kc -= g.nkc[gi++];
+    }
     const int per_group = 8 * g.ntn;
     const int group = lid / per_group, first_m = group * 8, gsize = min(g.ntm - first_m, 8);
     const int in = lid - group * per_group;
@@ -128,16 +142,21 @@ __global__ __launch_bounds__(G::NT, G::NT / 256) void lora_gemm_mid_kernel(MidAr
     tni = in / gsize;
   }
   gi = __builtin_amdgcn_readfirstlane(gi);
-  const uint16_t* const X = g.ga.x[gi];
-  const uint16_t* const Wt = g.ga.W[gi];
+  kc = __builtin_amdgcn_readfirstlane(kc);
+  // LDK values per row in memory, K of them from column kbeg on for this workgroup
+  const int LDK = MODE == PART ? g.kall[gi] : g.ga.K;
+  const int kbeg = MODE == PART ? kc * g.kch[gi] : 0;
+  const int K = MODE == PART ? min(g.kch[gi], LDK - kbeg) : LDK;
+  const uint16_t* const X = g.ga.x[gi] + kbeg;
+  const uint16_t* const Wt = g.ga.W[gi] + kbeg;
   const uint16_t* const At = g.ga.A[gi];
   const uint16_t* const Bt = g.ga.B[gi];
-  float* const y_off = g.ga.y_off[gi];
-  float* const y_on = g.ga.y_on[gi];
+  float* const y_off = g.ga.y_off[gi] + (MODE == PART ? (size_t)kc * M * N : 0);
+  float* const y_on = MODE == PART ? nullptr : g.ga.y_on[gi];
   const int m0 = __builtin_amdgcn_readfirstlane(tmi * TM);
   const int n0 = __builtin_amdgcn_readfirstlane(tni * TN);
   const int nkt = (K + BK - 1) / BK;
-  const bool lora = y_on != nullptr && (PRE ? g.ts[gi] != nullptr : RA > 0 && At != nullptr && Bt != nullptr);
+  const bool lora = y_on != nullptr && (MODE == PRE ? g.ts[gi] != nullptr : RA > 0 && At != nullptr && Bt != nullptr);
 
   // LDS chunk index of (row, 16-byte chunk c): the chunk is XOR-ed with bits of
   // the row so that the 16 lanes of a read phase (16 consecutive rows, one
@@ -153,9 +172,11 @@ __global__ __launch_bounds__(G::NT, G::NT / 256) void lora_gemm_mid_kernel(MidAr
   static_assert(G::XB % NW == 0 && G::WB % NW == 0, "copy j of every wave is of one operand");
   constexpr int XJ = G::XB / NW, WJ = G::WB / NW;
   const int rl = lane / CPR, pc = lane % CPR;
-  const int row_bytes = K * 2;
-  const i32x4_t xr = make_rsrc_raw(X + (size_t)m0 * K, (uint32_t)min(TM, M - m0) * K * 2u);
-  const i32x4_t wrs = make_rsrc_raw(Wt + (size_t)n0 * K, (uint32_t)min(TN, N - n0) * K * 2u);
+  const int row_bytes = LDK * 2;
+  const int wrows = MODE == PART ? max(0, min(TN, r - n0)) : min(TN, N - n0);
+  const i32x4_t xr = make_rsrc_raw(X + (size_t)m0 * LDK, ((uint32_t)min(TM, M - m0) * LDK - kbeg) * 2u);
+  const i32x4_t wrs =
+      make_rsrc_raw(Wt + (size_t)(wrows > 0 ? n0 : 0) * LDK, wrows > 0 ? ((uint32_t)wrows * LDK - kbeg) * 2u : 0u);
   const bool t_on = RA > 0 && lora;
   const i32x4_t ars = make_rsrc_raw(t_on ? At : nullptr, t_on ? (uint32_t)min(r, RA) * K * 2u : 0u);
   auto dma = [&](int stage, int kt, int j) __attribute__((always_inline)) {
@@ -400,7 +421,7 @@ __global__ __launch_bounds__(G::NT, G::NT / 256) void lora_gemm_mid_kernel(MidAr
     f32x4_t v[UPQ];
 #pragma unroll
     for (int k = 0; k < UPQ; ++k) v[k] = un[b * UPQ + k];
-    if (y_off) store(y_off, v);
+    if (MODE == PART || y_off) store(y_off, v);
     if (!y_on) return;
     if (lora) {
       // s T B^T of the whole 32 x 32 block; this wave adds the units it holds.
@@ -408,7 +429,7 @@ __global__ __launch_bounds__(G::NT, G::NT / 256) void lora_gemm_mid_kernel(MidAr
       f32x16_t L;
 #pragma unroll
       for (int e = 0; e < 16; ++e) L[e] = 0.f;
-      if constexpr (PRE) {
+      if constexpr (MODE == PRE) {
         const int rp = g.rp;
         const int mr = __builtin_amdgcn_readfirstlane(m0 + wr * WM + mi * 32);
         const int nr = __builtin_amdgcn_readfirstlane(n0 + wc * WN + ni * 32);
@@ -487,28 +508,47 @@ float tile_cost(const MidTile& c, int M, int N, int K) {
   return c.base + (float)((tiles + 255) / 256) * (c.fixed + (float)((K + 63) / 64) * c.step);
 }
 
-template <class G, bool PRE>
+template <class G, MidMode MODE>
 void launch_tile(MidArgs& g, hipStream_t stream) {
+  int members = g.ga.G;  // (member, chunk) pairs of the pre-pass
+  if constexpr (MODE == PART) {
+    members = 0;
+    for (int i = 0; i < g.ga.G; ++i) members += g.nkc[i];
+  }
   g.ntm = (g.ga.M + G::TM - 1) / G::TM;
   g.ntn = (g.ga.N + G::TN - 1) / G::TN;
-  hipLaunchKernelGGL((lora_gemm_mid_kernel<G, PRE>), dim3(g.ntm * g.ntn * g.ga.G), dim3(G::NT), 0, stream, g);
+  hipLaunchKernelGGL((lora_gemm_mid_kernel<G, MODE>), dim3(g.ntm * g.ntn * members), dim3(G::NT), 0, stream, g);
 }
 
 template <int TM, int TN, int WM, int WN, int KS, int BK, int NS>
 hipError_t launch_mid(MidArgs& g, int ra, hipStream_t stream) {
-  if (g.rp > 0)
-    launch_tile<GemmMid<TM, TN, WM, WN, KS, BK, NS, 0>, true>(g, stream);
+  if (g.nkc[0] > 0)
+    launch_tile<GemmMid<TM, TN, WM, WN, KS, BK, NS, 0>, PART>(g, stream);
+  else if (g.rp > 0)
+    launch_tile<GemmMid<TM, TN, WM, WN, KS, BK, NS, 0>, PRE>(g, stream);
   else if (ra == 0)
-    launch_tile<GemmMid<TM, TN, WM, WN, KS, BK, NS, 0>, false>(g, stream);
+    launch_tile<GemmMid<TM, TN, WM, WN, KS, BK, NS, 0>, PLAIN>(g, stream);
   else if (ra == 16)
-    launch_tile<GemmMid<TM, TN, WM, WN, KS, BK, NS, 16>, false>(g, stream);
+    launch_tile<GemmMid<TM, TN, WM, WN, KS, BK, NS, 16>, PLAIN>(g, stream);
   else if (ra == 32)
-    launch_tile<GemmMid<TM, TN, WM, WN, KS, BK, NS, 32>, false>(g, stream);
+    launch_tile<GemmMid<TM, TN, WM, WN, KS, BK, NS, 32>, PLAIN>(g, stream);
   else if (ra == 64)
-    launch_tile<GemmMid<TM, TN, WM, WN, KS, BK, NS, 64>, false>(g, stream);
+    launch_tile<GemmMid<TM, TN, WM, WN, KS, BK, NS, 64>, PLAIN>(g, stream);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();
+}
+
+hipError_t launch_any(MidArgs& g, int ra, int tile, hipStream_t stream) {
+  switch (tile) {
+    case 0: return launch_mid<32, 32, 32, 32, 4, 128, 5>(g, ra, stream);
+    case 1: return launch_mid<32, 64, 32, 64, 4, 128, 5>(g, ra, stream);
+    case 2: return launch_mid<64, 64, 32, 64, 4, 128, 4>(g, ra, stream);
+    case 3: return launch_mid<64, 128, 64, 64, 4, 64, 6>(g, ra, stream);
+    case 4: return launch_mid<128, 128, 64, 64, 2, 64, 5>(g, ra, stream);
+    case 5: return launch_mid<128, 192, 64, 96, 2, 64, 4>(g, ra, stream);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 }  // namespace
@@ -540,16 +580,38 @@ hipError_t launch_lora_gemm_mid(const GroupArgs& ga, const uint16_t* const* ts, 
              (reinterpret_cast<uintptr_t>(ga.y_on[i]) & 15) == 0;
     any_on = any_on || (ga.y_on[i] && ga.A[i] && ga.B[i]);
   }
-  const int ra = any_on ? padded_rank(ga.r) : 0;
-  switch (tile) {
-    case 0: return launch_mid<32, 32, 32, 32, 4, 128, 5>(g, ra, stream);
-    case 1: return launch_mid<32, 64, 32, 64, 4, 128, 5>(g, ra, stream);
-    case 2: return launch_mid<64, 64, 32, 64, 4, 128, 4>(g, ra, stream);
-    case 3: return launch_mid<64, 128, 64, 64, 4, 64, 6>(g, ra, stream);
-    case 4: return launch_mid<128, 128, 64, 64, 2, 64, 5>(g, ra, stream);
-    case 5: return launch_mid<128, 192, 64, 96, 2, 64, 4>(g, ra, stream);
-    default: return hipErrorInvalidValue;
+  return launch_any(g, any_on ? padded_rank(ga.r) : 0, tile, stream);
+}
+
+hipError_t launch_t_part_mid(const TpreArgs* as, int n, int rp, int* nkc, hipStream_t stream) {
+  MidArgs g{};
+  g.ga.G = n;
+  g.ga.M = as[0].M;
+  g.ga.N = rp;
+  g.ga.r = as[0].r;
+  g.vec4 = 1;  // rows of rp fp32 in a 16-byte aligned workspace
+  // 64 x 64 tiles and as many K chunks (up to 8, each of at least 256) as give
+  // at most 256 workgroups; 128 x 128 tiles where those would not fit one round
+  // unsplit.  Whole linear with pre-pass, us: M = 4096, K = N = 2048, rank 128
+  // 56.3 with 2 chunks, 60.6 with 4, 69 with 8, 61.6 for 128 x 128 in 8 chunks;
+  // 3000 x 4096 x 4096, rank 64 126 with 4 chunks against 130; 1024 x 4096 x
+  // 4096, rank 128 63.3 with 8 chunks against 64.0 with 4.  Tile and chunks
+  // depend on M, K and rp alone, so that T has the same bits in every group.
+  const int rows64 = (as[0].M + 63) / 64 * (rp / 64);
+  const int tile = rp == 128 && rows64 > 256 ? 4 : 2;
+  const int tiles = tile == 4 ? (as[0].M + 127) / 128 : rows64;
+  const int most = tiles >= 256 ? 1 : 256 / tiles < kTpreMaxChunks ? 256 / tiles : kTpreMaxChunks;
+  for (int j = 0; j < n; ++j) {
+    if (as[j].M != as[0].M || as[j].r != as[0].r) return hipErrorInvalidValue;
+    g.ga.x[j] = as[j].x;
+    g.ga.W[j] = as[j].A;
+    g.ga.y_off[j] = as[j].part;
+    g.kall[j] = as[j].K;
+    const int want = (as[j].K + 255) / 256 < most ? (as[j].K + 255) / 256 : most;
+    g.kch[j] = ((as[j].K + want - 1) / want + 63) / 64 * 64;
+    nkc[j] = g.nkc[j] = (as[j].K + g.kch[j] - 1) / g.kch[j];
   }
+  return launch_any(g, 0, tile, stream);
 }
 
 }  // namespace hydra

@@ -8,10 +8,8 @@
 //    workgroups share the work), 8 waves taking 32-wide k-steps in turn
 //    (v_mfma_f32_16x16x32_bf16, fp32 accumulation), their partial tiles
 //    summed in LDS in wave order and written to the workspace;
-//  * lora_t_part_wide_kernel (padded ranks 64, 128): one workgroup per 128
-//    rows and K chunk, each wave 32 rows x RP on v_mfma_f32_32x32x16_bf16,
-//    A staged in LDS per 256-wide sub-chunk, so that A is read once per 128
-//    rows;
+//  * padded ranks 64, 128: a GEMM of RP columns per K chunk on the smaller
+//    tiles of lora_gemm_mid.hip (launch_t_part_mid);
 //  * lora_t_finish_kernel: the chunk partials added in chunk order, s * T
 //    split into a bf16 hi part and a bf16 lo part (the rounding error of hi),
 //    so that the GEMM's bf16 MFMAs add s T B^T to within ~2^-16 relative;
@@ -109,148 +107,121 @@ __global__ __launch_bounds__(T_WAVES * 64) void lora_t_part_kernel(TpreJobs jobs
   t_part<RP>(jobs.a[j], jobs.kch[j], y - jobs.ybeg[j]);
 }
 
-// Wide ranks (RP = 64, 128): a workgroup of W_WAVES waves owns W_WAVES x 32
-// rows and one K chunk; each wave accumulates its 32 rows x RP columns of T
-// with v_mfma_f32_32x32x16_bf16 (A rows as the A operand, x rows as the B
-// operand).  The chunk goes in sub-chunks of W_SUB k: the workgroup stages
-// the sub-chunk of A ([RP x W_SUB], rows padded by 16 bytes so that the
-// 32-row fragment reads hit every bank once) in LDS, so A is read once per
-// W_WAVES x 32 rows (the 16-row form above reads it once per 16 rows: 8x
-// the x traffic at RP = 128).  Each wave holds the x slice and A pieces of
-// two sub-chunks in registers: the next one's loads are in flight while the
-// current one is staged and multiplied.
-constexpr int kWideFrom = 64;  // padded ranks from which the wide form runs
-constexpr int W_WAVES = 4;
-constexpr int W_ROWS = W_WAVES * 32;
-constexpr int W_SUB = 128;
-constexpr int W_LDA = W_SUB + 8;  // LDS row stride of the A sub-chunk (bf16)
-
-// K chunks of the wide form: at most kTpreMaxChunks, each at least 256 wide
-// (a multiple of the 16-wide k-step), so that small M still spreads over
-// many workgroups.
-inline void tpre_wide_chunks(int K, int& nkc, int& kch) {
-  const int want = (K + 255) / 256;
-  nkc = want < kTpreMaxChunks ? want : kTpreMaxChunks;
-  kch = ((K + nkc - 1) / nkc + 15) / 16 * 16;
-  nkc = (K + kch - 1) / kch;
-}
-
+// B zero padded to RP columns, by `blocks` workgroups of `threads` threads.
 template <int RP>
-__device__ __forceinline__ void t_part_wide(const TpreArgs& a, int kch, int kc) {
-  constexpr int RA = RP < 32 ? 32 : RP;            // rows of A staged (rows RP.. read as zeros)
-  constexpr int TJ = RA / 32;
-  constexpr int XS = W_SUB / 16;                   // 16-wide k-steps per sub-chunk
-  constexpr int AV = RA * (W_SUB / 8) / (W_WAVES * 64);  // 16-byte pieces of A per thread per sub-chunk
-  static_assert(AV * W_WAVES * 64 == RA * (W_SUB / 8), "the A sub-chunk splits evenly over the threads");
-  __shared__ uint16_t as[RA][W_LDA];
-  const int M = a.M, K = a.K;
-  const int t = threadIdx.x;
-  const int lane = t & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-  const int l32 = lane & 31, lh = lane >> 5;
-  // (made provably wave-uniform: the descriptor built from them must live in
-  // SGPRs, or every load becomes a loop over the lanes' descriptors)
-  const int m0 = __builtin_amdgcn_readfirstlane(blockIdx.x * W_ROWS + wave * 32);
-  const int rows = __builtin_amdgcn_readfirstlane(max(0, min(32, M - m0)));
-  const __amdgpu_buffer_rsrc_t xrs = make_rsrc(a.x + (size_t)min(m0, M) * K, (uint32_t)rows * K * 2u);
-  const __amdgpu_buffer_rsrc_t ars = make_rsrc(a.A, (uint32_t)min(a.r, RP) * K * 2u);
-  f32x16_t acc[TJ];
-#pragma unroll
-  for (int j = 0; j < TJ; ++j)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) acc[j][i] = 0.f;
-  const int k_begin = kc * kch;
-  const int k_end = min(K, k_begin + kch);
-  // x slice and A pieces of the sub-chunk at kb into registers
-  auto load = [&](int kb, uint4 (&xf)[XS], uint4 (&av)[AV]) __attribute__((always_inline)) {
-#pragma unroll
-    for (int u = 0; u < XS; ++u) {
-      const int k = kb + u * 16 + lh * 8;
-      xf[u] = buf_load16(xrs, k < k_end ? (l32 * K + k) * 2 : kOutOfRange);
-    }
-#pragma unroll
-    for (int i = 0; i < AV; ++i) {
-      const int c = t + i * W_WAVES * 64;
-      const int row = c / (W_SUB / 8), k = kb + (c % (W_SUB / 8)) * 8;
-      av[i] = buf_load16(ars, k < k_end ? (row * K + k) * 2 : kOutOfRange);
-    }
-  };
-  // A pieces into LDS (after every wave is done with the previous sub-chunk), then the MFMAs
-  auto stage_and_multiply = [&](const uint4 (&xf)[XS], const uint4 (&av)[AV]) __attribute__((always_inline)) {
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < AV; ++i) {
-      const int c = t + i * W_WAVES * 64;
-      *reinterpret_cast<uint4*>(&as[c / (W_SUB / 8)][(c % (W_SUB / 8)) * 8]) = av[i];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < XS; ++u)
-#pragma unroll
-      for (int j = 0; j < TJ; ++j)
-        acc[j] = mfma32(*reinterpret_cast<const uint4*>(&as[j * 32 + l32][u * 16 + lh * 8]), xf[u], acc[j]);
-  };
-  // two register sets: the next sub-chunk's loads are in flight while the current one is staged and multiplied
-  uint4 xf0[XS], av0[AV], xf1[XS], av1[AV];
-  if (k_begin < k_end) load(k_begin, xf0, av0);
-  for (int kb = k_begin; kb < k_end; kb += 2 * W_SUB) {
-    const int kb1 = kb + W_SUB;
-    if (kb1 < k_end) load(kb1, xf1, av1);
-    stage_and_multiply(xf0, av0);
-    if (kb1 >= k_end) break;
-    if (kb1 + W_SUB < k_end) load(kb1 + W_SUB, xf0, av0);
-    stage_and_multiply(xf1, av1);
+__device__ __forceinline__ void pad_b(const TpreArgs& a, size_t block, size_t blocks, int threads) {
+  const size_t total = (size_t)a.N * RP;
+  for (size_t e = block * threads + threadIdx.x; e < total; e += blocks * threads) {
+    const int n = (int)(e / RP), j = (int)(e % RP);
+    a.bp[e] = j < a.r ? a.B[(size_t)n * a.r + j] : (uint16_t)0;
   }
-  // acc[j] element 4 i + e holds T[m0 + l32][32 j + 8 i + 4 lh + e]
-  const int row = m0 + l32;
-  if (row >= M) return;
-  float* out = a.part + ((size_t)kc * M + row) * RP;
-#pragma unroll
-  for (int j = 0; j < TJ; ++j)
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      if (32 * j + 8 * i < RP)
-        *reinterpret_cast<float4*>(out + 32 * j + 8 * i + 4 * lh) =
-            make_float4(acc[j][4 * i], acc[j][4 * i + 1], acc[j][4 * i + 2], acc[j][4 * i + 3]);
 }
 
-template <int RP>
-__global__ __launch_bounds__(W_WAVES * 64) void lora_t_part_wide_kernel(TpreJobs jobs) {
-  const int y = blockIdx.y;
-  const int j = job_of(jobs.ybeg, jobs.n, y);
-  t_part_wide<RP>(jobs.a[j], jobs.kch[j], y - jobs.ybeg[j]);
+// hi and lo bf16 parts of s * T[row][j], written row-major (ts) and / or
+// transposed (tT, whose rows M..Mp are written as zeros: v = 0 there).
+__device__ __forceinline__ void t_store(const TpreArgs& a, int rp, size_t row, size_t j, float v) {
+  v *= a.s;
+  const uint32_t hi = f32_to_bf16_rne(v);
+  const uint32_t lo = f32_to_bf16_rne(v - bf16_to_f32(hi));
+  if (a.ts && row < (size_t)a.M) {
+    a.ts[row * 2 * rp + j] = (uint16_t)hi;
+    a.ts[row * 2 * rp + rp + j] = (uint16_t)lo;
+  }
+  if (a.tT) {
+    a.tT[j * a.Mp + row] = (uint16_t)hi;
+    a.tT[(rp + j) * a.Mp + row] = (uint16_t)lo;
+  }
 }
 
 // s * T of element e = row * RP + j from the chunk partials (added in chunk
-// order), split into bf16 hi and lo parts, written row-major (ts) and / or
-// transposed (tT, whose rows M..Mp are written as zeros).
+// order).
 template <int RP>
 __device__ __forceinline__ void t_finish(const TpreArgs& a, int nkc, size_t e) {
   const int rows = a.tT ? a.Mp : a.M;
   if (e >= (size_t)rows * RP) return;
   const size_t row = e / RP, j = e % RP;
-  uint32_t hi = 0, lo = 0;
+  float v = 0.f;
   if (row < (size_t)a.M) {
     // all chunk loads in flight (nkc <= kTpreMaxChunks), then added in chunk order
     float p[kTpreMaxChunks];
 #pragma unroll
     for (int c = 0; c < kTpreMaxChunks; ++c) p[c] = c < nkc ? a.part[((size_t)c * a.M + row) * RP + j] : 0.f;
-    float v = 0.f;
 #pragma unroll
     for (int c = 0; c < kTpreMaxChunks; ++c)
       if (c < nkc) v += p[c];
-    v *= a.s;
-    hi = f32_to_bf16_rne(v);
-    lo = f32_to_bf16_rne(v - bf16_to_f32(hi));
-    if (a.ts) {
-      a.ts[row * 2 * RP + j] = (uint16_t)hi;
-      a.ts[row * 2 * RP + RP + j] = (uint16_t)lo;
+  }
+  t_store(a, RP, row, j, v);
+}
+
+// The whole pre-pass in one launch, without partial sums in memory, where K is
+// short (use_small below).  A workgroup of 16 waves owns 16 rows and JT * 16 of
+// the RP columns; the waves take the 32-wide k-steps in turn, S_UNROLL at a
+// time, and their tiles are summed in LDS in wave order.
+constexpr int S_WAVES = 16;
+constexpr int S_UNROLL = 8;
+constexpr int small_jt(int rp) { return rp >= 32 ? 2 : 1; }
+
+template <int RP>
+__global__ __launch_bounds__(S_WAVES * 64) void lora_t_small_kernel(TpreJobs jobs) {
+  constexpr int JT = small_jt(RP), JG = RP / 16 / JT;  // column groups
+  __shared__ f32x4_t red[S_WAVES][JT][64];
+  const int nb = jobs.bbeg[jobs.n];
+  if ((int)blockIdx.x >= nb) {
+    pad_b<RP>(jobs.a[0], blockIdx.x - nb, gridDim.x - nb, S_WAVES * 64);
+    return;
+  }
+  const int jb = job_of(jobs.bbeg, jobs.n, blockIdx.x);
+  const TpreArgs& a = jobs.a[jb];
+  const int b = blockIdx.x - jobs.bbeg[jb];
+  const int M = a.M, K = a.K;
+  const int t = threadIdx.x, lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int l16 = lane & 15, lg = lane >> 4;
+  const int m0 = b / JG * 16, j0 = b % JG * JT * 16;
+  const int rows = max(0, min(16, M - m0));
+  const __amdgpu_buffer_rsrc_t hrs = make_rsrc(a.x + (size_t)min(m0, M) * K, (uint32_t)rows * K * 2u);
+  const int arows = max(0, min(a.r - j0, JT * 16));
+  const __amdgpu_buffer_rsrc_t ars = make_rsrc(a.A + (size_t)min(j0, a.r) * K, (uint32_t)arows * K * 2u);
+  f32x4_t acc[JT];
+#pragma unroll
+  for (int j = 0; j < JT; ++j) acc[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  const int nks = (K + 31) / 32;
+  for (int k0 = wave; k0 < nks; k0 += S_WAVES * S_UNROLL) {
+    uint4 hf[S_UNROLL], af[S_UNROLL][JT];
+#pragma unroll
+    for (int u = 0; u < S_UNROLL; ++u) {
+      const int k = (k0 + u * S_WAVES) * 32 + lg * 8;
+      hf[u] = buf_load16(hrs, k < K ? (l16 * K + k) * 2 : kOutOfRange);
+#pragma unroll
+      for (int j = 0; j < JT; ++j) af[u][j] = buf_load16(ars, k < K ? ((j * 16 + l16) * K + k) * 2 : kOutOfRange);
     }
+#pragma unroll
+    for (int u = 0; u < S_UNROLL; ++u)
+#pragma unroll
+      for (int j = 0; j < JT; ++j) acc[j] = mfma16(hf[u], af[u][j], acc[j]);
   }
-  if (a.tT) {
-    a.tT[j * a.Mp + row] = (uint16_t)hi;
-    a.tT[(RP + j) * a.Mp + row] = (uint16_t)lo;
-  }
+  // acc[j] lane l holds T[m0 + 4 (l / 16) + i][j0 + 16 j + l % 16]
+#pragma unroll
+  for (int j = 0; j < JT; ++j) red[wave][j][lane] = acc[j];
+  __syncthreads();
+  if (t >= 16 * JT * 16) return;
+  const int rl = t / (JT * 16), j = t % (JT * 16);
+  const int src = (rl >> 2) * 16 + (j & 15);
+  float v = 0.f;
+#pragma unroll
+  for (int w = 0; w < S_WAVES; ++w) v += red[w][j >> 4][src][rl & 3];
+  const int row = m0 + rl;
+  if (row < (a.tT ? a.Mp : M)) t_store(a, RP, row, j0 + j, v);
+}
+
+// Where the one launch is faster than partial sums + finish (and the gap of
+// about 1.5 us between them), us at M = 1024: rank 16, K = 2048 7.0 against 4.6
+// + 4.1, K = 4096 9.7 against 4.8 + 5.0, K = 8192 16.7 against 6.0 + 4.9; rank
+// 128, K = 2048 9.9 against 5.8 + 4.8 (M = 2048: 18.1 against 7 + 5: two rounds
+// of workgroups).
+bool use_small(int M, int K, int rp) {
+  if (rp <= 32) return K <= 4096;
+  return K <= 2048 && (int64_t)M * rp <= 1024 * 128;
 }
 
 // Workgroups [bbeg[j], bbeg[j + 1]) finish job j; those past the last job's
@@ -265,45 +236,47 @@ __global__ __launch_bounds__(256) void lora_t_finish_kernel(TpreJobs jobs) {
     t_finish<RP>(jobs.a[j], jobs.nkc[j], (size_t)(b - jobs.bbeg[j]) * 256 + threadIdx.x);
     return;
   }
-  const TpreArgs& a0 = jobs.a[0];
-  const size_t total = (size_t)a0.N * RP;
-  const size_t nb = gridDim.x - nb_fin;
-  for (size_t e = (size_t)(b - nb_fin) * 256 + threadIdx.x; e < total; e += nb * 256) {
-    const int n = (int)(e / RP), j = (int)(e % RP);
-    a0.bp[e] = j < a0.r ? a0.B[(size_t)n * a0.r + j] : (uint16_t)0;
-  }
+  pad_b<RP>(jobs.a[0], b - nb_fin, gridDim.x - nb_fin, 256);
 }
 
 template <int RP>
 hipError_t launch_rp(const TpreArgs* as, int n, const uint16_t** bp_used, hipStream_t stream) {
-  constexpr bool wide = RP >= kWideFrom;
+  constexpr bool wide = RP >= 64;
   TpreJobs jobs{};
   jobs.n = n;
-  jobs.ybeg[0] = 0;
-  jobs.bbeg[0] = 0;
-  for (int j = 0; j < n; ++j) {
-    jobs.a[j] = as[j];
-    (wide ? tpre_wide_chunks : tpre_chunks)(as[j].K, jobs.nkc[j], jobs.kch[j]);
-    jobs.ybeg[j + 1] = jobs.ybeg[j] + jobs.nkc[j];
-    jobs.bbeg[j + 1] = jobs.bbeg[j] + (int)(((size_t)(as[j].tT ? as[j].Mp : as[j].M) * RP + 255) / 256);
-  }
-  const int M = as[0].M;  // (every job has the same rows)
-  if constexpr (wide)
-    hipLaunchKernelGGL((lora_t_part_wide_kernel<RP>), dim3((M + W_ROWS - 1) / W_ROWS, jobs.ybeg[n]),
-                       dim3(W_WAVES * 64), 0, stream, jobs);
-  else
-    hipLaunchKernelGGL((lora_t_part_kernel<RP>), dim3((M + 15) / 16, jobs.ybeg[n]), dim3(T_WAVES * 64), 0, stream,
-                       jobs);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
   // B serves as its own padded copy when its rows already are RP bf16, 16-byte
   // aligned; no B at all (B null): nothing to pad.  Only a single job pads.
   const TpreArgs& a0 = as[0];
   const bool direct = n > 1 || a0.B == nullptr || (a0.r == RP && (reinterpret_cast<uintptr_t>(a0.B) & 15) == 0);
   if (bp_used) *bp_used = a0.B == nullptr ? nullptr : direct ? a0.B : a0.bp;
-  const size_t total = (size_t)a0.N * RP;
-  const int bblocks = direct ? 0 : (int)((total + 255) / 256 < 2048 ? (total + 255) / 256 : 2048);
-  hipLaunchKernelGGL((lora_t_finish_kernel<RP>), dim3(jobs.bbeg[n] + bblocks), dim3(256), 0, stream, jobs);
+  const int M = a0.M;  // (every job has the same rows)
+  const size_t pads = ((size_t)a0.N * RP + 255) / 256;
+  const int pad_blocks = direct ? 0 : (int)(pads < 2048 ? pads : 2048);
+  if (use_small(M, a0.Kform > 0 ? a0.Kform : a0.K, RP)) {
+    for (int j = 0; j < n; ++j) {
+      jobs.a[j] = as[j];
+      jobs.bbeg[j + 1] = jobs.bbeg[j] + ((as[j].tT ? as[j].Mp : M) + 15) / 16 * (RP / 16 / small_jt(RP));
+    }
+    hipLaunchKernelGGL((lora_t_small_kernel<RP>), dim3(jobs.bbeg[n] + (pad_blocks + 3) / 4), dim3(S_WAVES * 64), 0,
+                       stream, jobs);
+    return hipGetLastError();
+  }
+  for (int j = 0; j < n; ++j) {
+    jobs.a[j] = as[j];
+    if (!wide) tpre_chunks(as[j].K, jobs.nkc[j], jobs.kch[j]);
+    jobs.ybeg[j + 1] = jobs.ybeg[j] + jobs.nkc[j];
+    jobs.bbeg[j + 1] = jobs.bbeg[j] + (int)(((size_t)(as[j].tT ? as[j].Mp : as[j].M) * RP + 255) / 256);
+  }
+  hipError_t e;
+  if constexpr (wide) {
+    e = launch_t_part_mid(as, n, RP, jobs.nkc, stream);
+  } else {
+    hipLaunchKernelGGL((lora_t_part_kernel<RP>), dim3((M + 15) / 16, jobs.ybeg[n]), dim3(T_WAVES * 64), 0, stream,
+                       jobs);
+    e = hipGetLastError();
+  }
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((lora_t_finish_kernel<RP>), dim3(jobs.bbeg[n] + pad_blocks), dim3(256), 0, stream, jobs);
   return hipGetLastError();
 }
 
