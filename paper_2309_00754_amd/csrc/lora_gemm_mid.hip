@@ -330,7 +330,40 @@ __global__ __launch_bounds__(G::NT, G::NT / 256) void lora_gemm_mid_kernel(MidAr
   char* const lds = reinterpret_cast<char*>(sm);
   uint16_t* const Bs = reinterpret_cast<uint16_t*>(lds);
   uint16_t* const Ts = reinterpret_cast<uint16_t*>(lds + G::BSB);
-  char* const scratch = lds + G::BSB + G::TSB;
+  char* scratch = lds + G::BSB + G::TSB;
+  // PRE: the tile's rows of ts ([hi | lo], 2 rp values) and of bp (rp values)
+  // go to LDS, swizzled like the slabs.  Read from memory per 32 x 32 block
+  // they cost 576 KB a workgroup at rank 128 on 128 x 192, here 112 KB.  The
+  // copies run during the reduce-scatter where both fit.
+  const int rp = MODE == PRE ? g.rp : 16;
+  const int lrp = 31 - __builtin_clz(rp);  // rp = 16, 32, 64 or 128
+  const int tcl = lrp - 2, bcl = lrp - 3;  // log2 of the 16-byte chunks per row of ts and bp
+  const int bs_at = TM << tcl;             // chunk of the first row of bp
+  auto up_swz = [](int row, int cl) __attribute__((always_inline)) {
+    return (row >> max(0, 4 - cl)) & ((1 << min(cl, 4)) - 1);
+  };
+  auto stage_update = [&]() __attribute__((always_inline)) {
+    const i32x4_t tr = make_rsrc_raw(g.ts[gi] + (size_t)m0 * 2 * rp, (uint32_t)min(TM, M - m0) * 4u * rp);
+    const i32x4_t br = make_rsrc_raw(g.bp[gi] + (size_t)n0 * rp, (uint32_t)min(TN, N - n0) * 2u * rp);
+    const int tb = (TM << tcl) / 64, bb = (TN << bcl) / 64;  // copies of 64 chunks
+    for (int b = wave; b < tb + bb; b += NW) {
+      const bool is_t = b < tb;
+      const int cl = is_t ? tcl : bcl;
+      const int at = (is_t ? b : b - tb) * 64 + lane;
+      const int row = at >> cl, c = (at & ((1 << cl) - 1)) ^ up_swz(row, cl);
+      dma16(is_t ? tr : br, sm + b * 64, ((row << cl) + c) * 16);
+    }
+  };
+  const bool staged = MODE == PRE && lora;
+  bool early = false;
+  if constexpr (MODE == PRE) {
+    const size_t bytes = (size_t)(bs_at + (TN << bcl)) * 16;
+    early = staged && bytes + G::EXB <= G::LDS;
+    if (early) {
+      scratch = lds + bytes;
+      stage_update();
+    }
+  }
   if constexpr (RA > 0) {
 #pragma unroll
     for (int i = 0; i < BPT; ++i)
@@ -393,6 +426,13 @@ __global__ __launch_bounds__(G::NT, G::NT / 256) void lora_gemm_mid_kernel(MidAr
     if constexpr (KS > 4) step(IC<4>{}, IC<NU / 8>{});
     static_assert(KS <= 8, "steps listed above");
   }
+  if (staged) {
+    if (!early) {
+      __syncthreads();  // every wave is done with the exchange buffer
+      stage_update();
+    }
+    mid_barrier<0>();
+  }
   constexpr int MYU = NU / KS;             // units held
   constexpr int MYQ = MYU >= 4 ? MYU / 4 : 1;  // sub-tile blocks they lie in
   constexpr int UPQ = MYU / MYQ;           // units per block
@@ -430,23 +470,19 @@ __global__ __launch_bounds__(G::NT, G::NT / 256) void lora_gemm_mid_kernel(MidAr
 #pragma unroll
       for (int e = 0; e < 16; ++e) L[e] = 0.f;
       if constexpr (MODE == PRE) {
-        const int rp = g.rp;
-        const int mr = __builtin_amdgcn_readfirstlane(m0 + wr * WM + mi * 32);
-        const int nr = __builtin_amdgcn_readfirstlane(n0 + wc * WN + ni * 32);
-        const __amdgpu_buffer_rsrc_t tr =
-            make_rsrc(g.ts[gi] + (size_t)min(mr, M) * 2 * rp, (uint32_t)max(0, min(32, M - mr)) * 4u * rp);
-        const __amdgpu_buffer_rsrc_t br =
-            make_rsrc(g.bp[gi] + (size_t)min(nr, N) * rp, (uint32_t)max(0, min(32, N - nr)) * 2u * rp);
-        for (int k0 = 0; k0 < 2 * rp; k0 += 64) {
-          uint4 tf[4], bf[4];
+        const int trow = wr * WM + mi * 32 + l32, brow = wc * WN + ni * 32 + l32;
+        const int tsw = up_swz(trow, tcl), bsw = up_swz(brow, bcl);
+        const int bmask = (1 << bcl) - 1;
+        for (int k0 = 0; k0 < (1 << tcl); k0 += 4) {  // chunks of 8 values: two 16-wide k-steps
+          uint4 tf[2], bf[2];
 #pragma unroll
-          for (int ks = 0; ks < 4; ++ks) {
-            const int k = k0 + ks * 16 + lh * 8;
-            tf[ks] = buf_load16(tr, k < 2 * rp ? (l32 * 2 * rp + k) * 2 : kOutOfRange);
-            bf[ks] = buf_load16(br, k < 2 * rp ? (l32 * rp + (k & (rp - 1))) * 2 : kOutOfRange);
+          for (int ks = 0; ks < 2; ++ks) {
+            const int ch = k0 + 2 * ks + lh;
+            tf[ks] = sm[(trow << tcl) + (ch ^ tsw)];
+            bf[ks] = sm[bs_at + (brow << bcl) + ((ch & bmask) ^ bsw)];
           }
 #pragma unroll
-          for (int ks = 0; ks < 4; ++ks) L = mfma32(bf[ks], tf[ks], L);
+          for (int ks = 0; ks < 2; ++ks) L = mfma32(bf[ks], tf[ks], L);
         }
       } else {
         constexpr int RA1 = RA > 0 ? RA : 1;
