@@ -5,6 +5,11 @@ libhydra.  Tensors are PyTorch tensors on a ROCm device (PyTorch provides the
 device memory and the stream); they are checked for dtype, shape, device and
 contiguity, then their data pointers are passed through.  There is no CPU
 fallback: a missing library raises ``HydraLibraryMissing``.
+
+The accepted form of a call goes through ``_hydra_native`` (native/binding.cpp),
+which makes the same checks and the same library call without ctypes; for
+anything else it answers ``SLOW`` and the Python checks below decide, with
+their messages.
 """
 from __future__ import annotations
 
@@ -142,6 +147,32 @@ def lib() -> ctypes.CDLL:
     return L
 
 
+_SLOW = -1000
+
+
+class _NoNative:
+    """Stands in for _hydra_native where it is not built: every call takes the Python path."""
+
+    def __getattr__(self, name):
+        return lambda *args: _SLOW
+
+
+_nat = None
+
+
+def _native():
+    """_hydra_native, loaded with the first call (it needs torch's libraries in the process)."""
+    global _nat
+    if _nat is None:
+        _torch()
+        try:
+            from . import _hydra_native as nat
+        except ImportError:
+            nat = _NoNative()
+        _nat = nat
+    return _nat
+
+
 def status_string(status: int) -> str:
     return lib().hydra_status_string(int(status)).decode()
 
@@ -208,6 +239,14 @@ def hydra_lora_linear(x, W, A, B, s: float, y_off=None, y_on=None, stream=None) 
     x [M,K], W [N,K], A [r,K], B [N,r]: bf16 (or 16-bit integer tensors holding
     bf16 bits); y_off, y_on [M,N] float32 outputs (either may be None).
     """
+    st = (_nat or _native()).lora_linear(x, W, A, B, s, y_off, y_on, None, stream, False)
+    if st == _SLOW:
+        return _hydra_lora_linear(x, W, A, B, s, y_off, y_on, stream)
+    if st != HYDRA_OK:
+        _check(st, "hydra_lora_linear")
+
+
+def _hydra_lora_linear(x, W, A, B, s, y_off, y_on, stream) -> None:
     torch = _torch()
     bf = _bf16_types()
     M, K = x.shape
@@ -233,6 +272,14 @@ def hydra_lora_linear_workspace_bytes(M: int, N: int, r: int) -> int:
 
 def hydra_lora_linear_ws(x, W, A, B, s: float, y_off=None, y_on=None, workspace=None, stream=None) -> None:
     """hydra_lora_linear with the pre-pass workspace (see include/hydra.h); allocates one if none is given."""
+    st = (_nat or _native()).lora_linear(x, W, A, B, s, y_off, y_on, workspace, stream, True)
+    if st == _SLOW:
+        return _hydra_lora_linear_ws(x, W, A, B, s, y_off, y_on, workspace, stream)
+    if st != HYDRA_OK:
+        _check(st, "hydra_lora_linear_ws")
+
+
+def _hydra_lora_linear_ws(x, W, A, B, s, y_off, y_on, workspace, stream) -> None:
     torch = _torch()
     bf = _bf16_types()
     M, K = x.shape
@@ -267,6 +314,14 @@ def hydra_lora_linear_group(xs, Ws, As, Bs, ss, y_offs=None, y_ons=None, stream=
     xs, Ws, As, Bs, y_offs, y_ons: sequences of G tensors (entries may be None);
     ss: G scales.
     """
+    st = (_nat or _native()).lora_linear_group(xs, Ws, As, Bs, ss, y_offs, y_ons, None, stream, False)
+    if st == _SLOW:
+        return _hydra_lora_linear_group(xs, Ws, As, Bs, ss, y_offs, y_ons, stream)
+    if st != HYDRA_OK:
+        _check(st, "hydra_lora_linear_group")
+
+
+def _hydra_lora_linear_group(xs, Ws, As, Bs, ss, y_offs, y_ons, stream) -> None:
     torch = _torch()
     bf = _bf16_types()
     G = len(Ws)
@@ -308,6 +363,14 @@ def hydra_lora_linear_group_ws(xs, Ws, As, Bs, ss, y_offs=None, y_ons=None, work
     """hydra_lora_linear_group with a caller workspace: a decode step (M <= 8) in one launch (see include/hydra.h).
 
     workspace: a uint8 tensor from hydra_lora_linear_group_workspace (zero before its first use)."""
+    st = (_nat or _native()).lora_linear_group(xs, Ws, As, Bs, ss, y_offs, y_ons, workspace, stream, True)
+    if st == _SLOW:
+        return _hydra_lora_linear_group_ws(xs, Ws, As, Bs, ss, y_offs, y_ons, workspace, stream)
+    if st != HYDRA_OK:
+        _check(st, "hydra_lora_linear_group_ws")
+
+
+def _hydra_lora_linear_group_ws(xs, Ws, As, Bs, ss, y_offs, y_ons, workspace, stream) -> None:
     torch = _torch()
     bf = _bf16_types()
     G = len(Ws)
@@ -369,6 +432,14 @@ def hydra_lora_linear_multi(x_off, W, x_ons, As, Bs, ss, y_off=None, y_ons=None,
     x_off, y_off: tensors or None (together); x_ons, As, Bs, y_ons: sequences of n_on tensors (As, Bs may be
     None or all-None when r == 0); ss: n_on scales.
     """
+    st = (_nat or _native()).lora_linear_multi(x_off, W, x_ons, As, Bs, ss, y_off, y_ons, None, stream, False)
+    if st == _SLOW:
+        return _hydra_lora_linear_multi(x_off, W, x_ons, As, Bs, ss, y_off, y_ons, stream)
+    if st != HYDRA_OK:
+        _check(st, "hydra_lora_linear_multi")
+
+
+def _hydra_lora_linear_multi(x_off, W, x_ons, As, Bs, ss, y_off, y_ons, stream) -> None:
     st = lib().hydra_lora_linear_multi(*_multi_args(x_off, W, x_ons, As, Bs, ss, y_off, y_ons), _stream_handle(stream))
     _check(st, "hydra_lora_linear_multi")
 
@@ -385,6 +456,14 @@ def hydra_lora_linear_multi_ws(x_off, W, x_ons, As, Bs, ss, y_off=None, y_ons=No
     """hydra_lora_linear_multi with a caller workspace (rank 128 at every M; see include/hydra.h).
 
     workspace: a uint8 tensor of at least hydra_lora_linear_multi_workspace_bytes(M, N, r) bytes."""
+    st = (_nat or _native()).lora_linear_multi(x_off, W, x_ons, As, Bs, ss, y_off, y_ons, workspace, stream, True)
+    if st == _SLOW:
+        return _hydra_lora_linear_multi_ws(x_off, W, x_ons, As, Bs, ss, y_off, y_ons, workspace, stream)
+    if st != HYDRA_OK:
+        _check(st, "hydra_lora_linear_multi_ws")
+
+
+def _hydra_lora_linear_multi_ws(x_off, W, x_ons, As, Bs, ss, y_off, y_ons, workspace, stream) -> None:
     torch = _torch()
     if workspace is None:
         raise ValueError("hydra_lora_linear_multi_ws needs a workspace")
@@ -404,6 +483,17 @@ def hydra_score(h, W_lm, A, B, s: float, tokens, w_rm, n_seq: int, seq_len: int,
                 lp_on, lp_off, kl, reward=None, lse_on=None, lse_off=None,
                 workspace=None, err_flag=None, stream=None) -> None:
     """Fused CLM-head (LoRA on and off) log-prob / KL scoring plus the reward head."""
+    st = (_nat or _native()).score(None, h, W_lm, A, B, s, tokens, w_rm, n_seq, seq_len, lp_on, lp_off, kl, reward,
+                                   lse_on, lse_off, workspace, err_flag, stream, False)
+    if st == _SLOW:
+        return _hydra_score(h, W_lm, A, B, s, tokens, w_rm, n_seq, seq_len, lp_on, lp_off, kl, reward, lse_on,
+                            lse_off, workspace, err_flag, stream)
+    if st != HYDRA_OK:
+        _check(st, "hydra_score")
+
+
+def _hydra_score(h, W_lm, A, B, s, tokens, w_rm, n_seq, seq_len, lp_on, lp_off, kl, reward, lse_on, lse_off,
+                 workspace, err_flag, stream) -> None:
     torch = _torch()
     bf = _bf16_types()
     M, K = h.shape
@@ -437,6 +527,18 @@ def hydra_score_two_input(h_act, h_off, W_lm, A, B, s: float, tokens, w_rm, n_se
                           workspace=None, err_flag=None, stream=None) -> None:
     """Scoring with the actor pass's own hidden states (h_act, with the head's LoRA) and the LoRA-off pass's (h_off:
     reference log-probabilities and reward), one launch over both (see include/hydra.h)."""
+    st = (_nat or _native()).score(h_act, h_off, W_lm, A, B, s, tokens, w_rm, n_seq, seq_len, lp_on, lp_off, kl,
+                                   reward,
+                                   lse_on, lse_off, workspace, err_flag, stream, False) if h_act is not None else _SLOW
+    if st == _SLOW:
+        return _hydra_score_two_input(h_act, h_off, W_lm, A, B, s, tokens, w_rm, n_seq, seq_len, lp_on, lp_off, kl,
+                                      reward, lse_on, lse_off, workspace, err_flag, stream)
+    if st != HYDRA_OK:
+        _check(st, "hydra_score_two_input")
+
+
+def _hydra_score_two_input(h_act, h_off, W_lm, A, B, s, tokens, w_rm, n_seq, seq_len, lp_on, lp_off, kl, reward,
+                           lse_on, lse_off, workspace, err_flag, stream) -> None:
     torch = _torch()
     bf = _bf16_types()
     M, K = h_off.shape
@@ -469,6 +571,17 @@ def hydra_score_noalloc(h, W_lm, A, B, s: float, tokens, w_rm, n_seq: int, seq_l
                         lp_on, lp_off, kl, reward=None, lse_on=None, lse_off=None, err_flag=None,
                         stream=None) -> None:
     """hydra_score with its workspace in the library's own device scratch (no allocation by the call)."""
+    st = (_nat or _native()).score(None, h, W_lm, A, B, s, tokens, w_rm, n_seq, seq_len, lp_on, lp_off, kl, reward,
+                                   lse_on, lse_off, None, err_flag, stream, True)
+    if st == _SLOW:
+        return _hydra_score_noalloc(h, W_lm, A, B, s, tokens, w_rm, n_seq, seq_len, lp_on, lp_off, kl, reward, lse_on,
+                                    lse_off, err_flag, stream)
+    if st != HYDRA_OK:
+        _check(st, "hydra_score_noalloc")
+
+
+def _hydra_score_noalloc(h, W_lm, A, B, s, tokens, w_rm, n_seq, seq_len, lp_on, lp_off, kl, reward, lse_on, lse_off,
+                         err_flag, stream) -> None:
     torch = _torch()
     bf = _bf16_types()
     M, K = h.shape
@@ -495,6 +608,16 @@ def hydra_score_noalloc(h, W_lm, A, B, s: float, tokens, w_rm, n_seq: int, seq_l
 def hydra_score_logits(logits_on, logits_off, tokens, lp_on, lp_off, kl,
                        lse_on=None, lse_off=None, err_flag=None, stream=None) -> None:
     """Sampled-token log-probabilities and KL from materialised fp32 logits."""
+    st = (_nat or _native()).score_logits(logits_on, logits_off, tokens, lp_on, lp_off, kl, lse_on, lse_off, err_flag,
+                                          stream)
+    if st == _SLOW:
+        return _hydra_score_logits(logits_on, logits_off, tokens, lp_on, lp_off, kl, lse_on, lse_off, err_flag,
+                                   stream)
+    if st != HYDRA_OK:
+        _check(st, "hydra_score_logits")
+
+
+def _hydra_score_logits(logits_on, logits_off, tokens, lp_on, lp_off, kl, lse_on, lse_off, err_flag, stream) -> None:
     torch = _torch()
     M, V = logits_on.shape
     _need(logits_on, "logits_on", (torch.float32,))
@@ -510,6 +633,14 @@ def hydra_score_logits(logits_on, logits_off, tokens, lp_on, lp_off, kl,
 
 def hydra_value_head(h, w_v, values, stream=None) -> None:
     """values[m] = <h[m], w_v>: the critic's scalar head on every row (see include/hydra.h)."""
+    st = (_nat or _native()).value_head(h, w_v, values, stream)
+    if st == _SLOW:
+        return _hydra_value_head(h, w_v, values, stream)
+    if st != HYDRA_OK:
+        _check(st, "hydra_value_head")
+
+
+def _hydra_value_head(h, w_v, values, stream) -> None:
     torch = _torch()
     bf = _bf16_types()
     M, K = h.shape
@@ -524,6 +655,17 @@ def hydra_ppo_advantages(kl, reward, values, n_seq: int, seq_len: int, advantage
                          start: int = 0, beta: float = 0.02, gamma: float = 1.0, lam: float = 0.95,
                          stream=None) -> None:
     """Per-token PPO reward and GAE advantages / returns (see include/hydra.h)."""
+    st = (_nat or _native()).ppo_advantages(kl, reward, values, n_seq, seq_len, start, beta, gamma, lam, rewards,
+                                            advantages, returns, stream)
+    if st == _SLOW:
+        return _hydra_ppo_advantages(kl, reward, values, n_seq, seq_len, advantages, returns, rewards, start, beta,
+                                     gamma, lam, stream)
+    if st != HYDRA_OK:
+        _check(st, "hydra_ppo_advantages")
+
+
+def _hydra_ppo_advantages(kl, reward, values, n_seq, seq_len, advantages, returns, rewards, start, beta, gamma, lam,
+                          stream) -> None:
     torch = _torch()
     M = int(n_seq) * int(seq_len)
     for name, t, n in (("kl", kl, M), ("reward", reward, n_seq), ("values", values, M), ("advantages", advantages, M),
@@ -538,6 +680,17 @@ def hydra_ppo_advantages(kl, reward, values, n_seq: int, seq_len: int, advantage
 def hydra_ppo_loss(lp_new, lp_old, advantages, values, returns, n_seq: int, seq_len: int, losses, d_lp=None,
                    d_v=None, start: int = 0, eps: float = 0.2, stream=None) -> None:
     """PPO policy and value losses with their per-token gradients (see include/hydra.h)."""
+    st = (_nat or _native()).ppo_loss(lp_new, lp_old, advantages, values, returns, n_seq, seq_len, start, eps, losses,
+                                      d_lp, d_v, stream)
+    if st == _SLOW:
+        return _hydra_ppo_loss(lp_new, lp_old, advantages, values, returns, n_seq, seq_len, losses, d_lp, d_v, start,
+                               eps, stream)
+    if st != HYDRA_OK:
+        _check(st, "hydra_ppo_loss")
+
+
+def _hydra_ppo_loss(lp_new, lp_old, advantages, values, returns, n_seq, seq_len, losses, d_lp, d_v, start, eps,
+                    stream) -> None:
     torch = _torch()
     M = int(n_seq) * int(seq_len)
     for t, name in ((lp_new, "lp_new"), (lp_old, "lp_old"), (advantages, "advantages"), (values, "values"),
@@ -575,6 +728,14 @@ def hydra_lora_linear_backward(x, Wt, A, B, s: float, dy, dx=None, dA=None, dB=N
     dx [M,K], dA [r,K], dB [N,r] float32 outputs (each optional).  Allocates
     the workspace if none is given.
     """
+    st = (_nat or _native()).lora_linear_backward(x, Wt, A, B, s, dy, dx, dA, dB, workspace, stream)
+    if st == _SLOW:
+        return _hydra_lora_linear_backward(x, Wt, A, B, s, dy, dx, dA, dB, workspace, stream)
+    if st != HYDRA_OK:
+        _check(st, "hydra_lora_linear_backward")
+
+
+def _hydra_lora_linear_backward(x, Wt, A, B, s, dy, dx, dA, dB, workspace, stream) -> None:
     torch = _torch()
     bf = _bf16_types()
     M, N = dy.shape
