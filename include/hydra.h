@@ -80,8 +80,8 @@ typedef enum {
  * K >= 1, K % 8 == 0, K <= 2^21, 0 <= r <= HYDRA_MAX_RANK, and
  * ceil(M / 128) * ceil(N / 256) < 2^23 (the GEMM's tile grid fits one
  * dispatch; roughly M * N < 2^38).  With r == 0, y_on equals
- * y_off.  M <= 16 selects the bandwidth-bound (decode) kernels, larger M the
- * MFMA GEMM; both compute the same function.  At M > 16 with y_on and r > 64
+ * y_off.  M <= 8 (at r > 64 M <= 16) selects the bandwidth-bound (decode)
+ * kernels, larger M the MFMA GEMM; both compute the same function.  At M > 16 with y_on and r > 64
  * the update needs the pre-pass workspace of hydra_lora_linear_ws: this call
  * then returns HYDRA_ERR_WORKSPACE and launches nothing.
  */
@@ -138,7 +138,7 @@ hydra_status hydra_lora_linear_ws(const uint16_t* x, const uint16_t* W, const ui
  *   s                     HOST array of G scales
  * Member i computes exactly what hydra_lora_linear(x[i], W[i], A[i], B[i], s[i],
  * M, N, K, r, y_off[i], y_on[i]) computes.  Each member needs at least one
- * output.  M <= 16 runs one launch for the whole group; larger M one launch
+ * output.  M <= 8 runs one launch for the whole group; larger M one launch
  * too where the GEMM takes its smaller tiles, else the GEMM once per member.  Errors as in hydra_lora_linear; HYDRA_ERR_SHAPE for G out
  * of range.
  */

@@ -124,7 +124,7 @@ hydra_status group_check(int64_t G, const uint16_t* const* x, const uint16_t* co
   return HYDRA_OK;
 }
 
-// M > 16, padded rank <= 64: the members in one launch on the smaller tiles,
+// M > 8, padded rank <= 64: the members in one launch on the smaller tiles,
 // else one dual GEMM per member.
 hydra_status group_gemm(const hydra::GroupArgs& g, hipStream_t st) {
   const int tile = hydra::gemm_mid_tile(g.M, g.N, g.K);
@@ -161,13 +161,10 @@ hydra_status hydra_lora_linear_group(int64_t G, const uint16_t* const* x, const 
   const hydra_status chk = group_check(G, x, W, A, B, s, M, N, K, r, y_off, y_on, g, any_on);
   if (chk != HYDRA_OK) return chk;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-  if (M <= kDecodeMaxRows) {
-    // y_on of a member without an adapter equals its y_off: the kernel's
-    // update adds s * 0 there, because that member's A and B read as zeros.
-    if (!any_on) g.r = 0;
-    return from_hip(hydra::launch_lora_gemv_group(g, st));
-  }
-  if (any_on && hydra::padded_rank(g.r) > 64) return HYDRA_ERR_WORKSPACE;  // see hydra_lora_linear_ws
+  if (!any_on) g.r = 0;
+  const bool wide = hydra::padded_rank(g.r) > 64;
+  if (M <= hydra::kStreamRows || (M <= kDecodeMaxRows && wide)) return from_hip(hydra::launch_lora_gemv_group(g, st));
+  if (wide) return HYDRA_ERR_WORKSPACE;  // see hydra_lora_linear_ws
   return group_gemm(g, st);
 }
 
@@ -213,7 +210,7 @@ hydra_status hydra_lora_linear_group_ws(int64_t G, const uint16_t* const* x, con
   if (!any_on) g.r = 0;
   if (M <= hydra::kStreamRows) return from_hip(hydra::launch_gemv_fused(g, workspace, st));
   if (M <= kDecodeMaxRows) {
-    if (rp <= 64) return from_hip(hydra::launch_lora_gemv_group(g, st));
+    if (rp <= 64) return group_gemm(g, st);
     // rank 128 above 8 rows: the two row halves in turn
     hydra::GroupArgs lo = g, hi = g;
     lo.M = hydra::kStreamRows;

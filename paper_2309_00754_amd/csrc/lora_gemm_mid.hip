@@ -1,5 +1,5 @@
 // Dual-path LoRA GEMM for row counts whose 128 x 256 tiles would leave most of
-// the 256 CUs idle (prompts, mini-batches, generation batches above 16 rows).
+// the 256 CUs idle (prompts, mini-batches, generation batches above 8 rows).
 // Same function as lora_gemm_kernel on smaller tiles (GemmMid below): the
 // LoRA-off output x W^T and the LoRA-on output x W^T + s (x A^T) B^T from one
 // pass over W (Sec. 3, "Dynamic LoRA" and "Stage 2: Hydra-PPO").
@@ -18,8 +18,8 @@
 //    with a part of the sub-tile and the epilogue uses all of them;
 //  * LoRA: either T = x A^T is accumulated in the main loop
 //    (v_mfma_f32_16x16x32_bf16, the rows of A in the slab next to those of W)
-//    and s T meets B in the epilogue as bf16 hi + lo parts, or (PRE) the hi and
-//    lo parts of s T and the padded rows of B are read from the pre-pass's
+//    and s T meets B in the epilogue as bf16 parts, or (PRE) the hi and lo
+//    parts of s T and the padded rows of B are read from the pre-pass's
 //    workspace.
 // The K order of every output depends on the tile shape alone, and the shape
 // on M, N and K alone, so an output has the same bits whatever the entry point.
@@ -74,9 +74,13 @@ struct GemmMid {
   static constexpr int TSPLIT = SPW >= 2 ? 1 : 2;           // waves that share one of them
   static constexpr int TKS = KS / TSPLIT;                   // partial sums of T
   static constexpr int TPW = RA > 0 ? WM / 16 / NWN / TSPLIT : 1;  // 16-row T tiles per wave
-  static constexpr int BSB = TN * RA * 2, TSB = TM * 2 * RA * 2;   // bytes of B's and s T's LDS copies
   static constexpr int EXB = KS > 1 ? NW * NQ * 2 * 1024 : 0;      // exchange buffer of the reduce-scatter
   static constexpr int TRB = RA > 0 ? TKS * TM * RA * 4 : 0;       // partial T
+  // s T as bf16 parts, each the rounding error of the ones before: three of
+  // them hold all 24 bits (error of y_on against 64 bits 4e-7, with two 2.2e-6)
+  static constexpr int BSB = TN * RA * 2;                          // bytes of B's LDS copy
+  static constexpr int NP = BSB + TM * 3 * RA * 2 + cmax(EXB, TRB) <= 160 * 1024 ? 3 : 2;
+  static constexpr int TSB = TM * NP * RA * 2;                     // ... and of s T's
   static constexpr size_t EPI = BSB + TSB + cmax(EXB, TRB);
   static constexpr size_t kLds = 160 * 1024;
   // fewer stages where they do not fit with the rows of A; an even number where
@@ -106,7 +110,7 @@ template <class G, MidMode MODE>
 __global__ __launch_bounds__(G::NT, G::NT / 256) void lora_gemm_mid_kernel(MidArgs g) {
   constexpr int TM = G::TM, TN = G::TN, WM = G::WM, WN = G::WN, KS = G::KS, BK = G::BK, RA = G::RA;
   constexpr int NW = G::NW, NT = G::NT, MT = G::MT, NTL = G::NTL, NQ = G::NQ, CPR = G::CPR, RPB = G::RPB;
-  constexpr int NS = G::NS, STAGE = G::STAGE, SPW = G::SPW, DPW = G::DPW, NU = G::NU;
+  constexpr int NS = G::NS, STAGE = G::STAGE, SPW = G::SPW, DPW = G::DPW, NU = G::NU, NP = G::NP;
   constexpr int TJ = RA / 16, TJ1 = TJ > 0 ? TJ : 1, TPW = G::TPW, HS = G::HS;
   constexpr int XROW = 0, WROW = TM, AROW = TM + TN;
   __shared__ uint4 sm[G::LDS / 16];
@@ -383,11 +387,13 @@ __global__ __launch_bounds__(G::NT, G::NT / 256) void lora_gemm_mid_kernel(MidAr
 #pragma unroll
       for (int k2 = 1; k2 < G::TKS; ++k2) v += tp[k2 * TM * RA + e];
       v *= g.ga.s[gi];
-      const uint32_t hi = f32_to_bf16_rne(v);
-      const uint32_t lo = f32_to_bf16_rne(v - bf16_to_f32(hi));
       const int row = e / RA, j = e % RA;
-      Ts[row * 2 * RA + j] = (uint16_t)hi;
-      Ts[row * 2 * RA + RA + j] = (uint16_t)lo;
+#pragma unroll
+      for (int p = 0; p < NP; ++p) {
+        const uint32_t part = f32_to_bf16_rne(v);
+        Ts[(row * NP + p) * RA + j] = (uint16_t)part;
+        v -= bf16_to_f32(part);
+      }
     }
     __syncthreads();
   }
@@ -487,10 +493,10 @@ __global__ __launch_bounds__(G::NT, G::NT / 256) void lora_gemm_mid_kernel(MidAr
       } else {
         constexpr int RA1 = RA > 0 ? RA : 1;
 #pragma unroll
-        for (int ks = 0; ks < 2 * RA / 16; ++ks) {
+        for (int ks = 0; ks < NP * RA / 16; ++ks) {
           const int k = ks * 16 + lh * 8;
           const uint4 bf = *reinterpret_cast<const uint4*>(Bs + (wc * WN + ni * 32 + l32) * RA + k % RA1);
-          const uint4 tf = *reinterpret_cast<const uint4*>(Ts + (wr * WM + mi * 32 + l32) * 2 * RA + k);
+          const uint4 tf = *reinterpret_cast<const uint4*>(Ts + (wr * WM + mi * 32 + l32) * NP * RA + k);
           L = mfma32(bf, tf, L);
         }
       }
@@ -528,7 +534,10 @@ __global__ __launch_bounds__(G::NT, G::NT / 256) void lora_gemm_mid_kernel(MidAr
 // larger tile is cheaper per output as long as it still gives 256 tiles.
 // M x K x N, us: 48 x 4096 x 4096 41.4 -> 11.6, 333 x 4096 x 11008 72 -> 58,
 // 512 x 4096 x 4096 47.6 -> 29.9, 1000 x 11008 x 4096 157 -> 121, 500 x 2048 x
-// 2048 30.2 -> 13.6 (128 x 256 tile -> here, rank 16).
+// 2048 30.2 -> 13.6 (128 x 256 tile -> here, rank 16).  Rows 9 to 16, against
+// a kernel whose 16 waves split K over 16 to 64 columns: four 4096 x 4096 40.2
+// -> 38.4 at rank 16, 52.9 -> 51.2 at rank 64; four 2048 x 2048 14.5 -> 10.8
+// and 23.0 -> 15.0; one 512 x 512 7.7 -> 6.2.
 struct MidTile {
   int tm, tn;
   float base, fixed, step;

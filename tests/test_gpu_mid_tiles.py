@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 
 # (M, N, K) by the tile that the size model picks: one with remainders in both directions, one of whole tiles
 SHAPES = [
-    (17, 33, 8), (31, 700, 72), (64, 96, 1536),               # 32 x 32
+    (9, 40, 264), (16, 512, 512), (17, 33, 8), (31, 700, 72), (64, 96, 1536),  # 32 x 32
     (65, 5000, 264), (96, 4096, 128),                         # 32 x 64
     (40, 8200, 136), (128, 8192, 1032),                       # 64 x 64
     (200, 5000, 264), (300, 5001, 1000), (128, 16384, 128),   # 64 x 128
