@@ -91,21 +91,4 @@ constexpr float kLog2e = 1.4426950408889634f;
 __device__ __forceinline__ float exp_e(float x) { return __builtin_amdgcn_exp2f(x * kLog2e); }
 __device__ __forceinline__ float log_e(float x) { return __builtin_amdgcn_logf(x) * 0.6931471805599453f; }
 
-// Merge two (running max, sum of exp(v - max)) pairs.  The products and the
-// sum are rounded separately (no contraction), so merge(a, b) == merge(b, a)
-// bit for bit.  An empty side has m = -inf and s = 0.
-__device__ __forceinline__ void lse_merge(float& m, float& s, float m2, float s2) {
-#pragma clang fp contract(off)
-  const float mn = fmaxf(m, m2);
-  if (mn == -INFINITY) {
-    m = mn;
-    s = 0.f;
-    return;
-  }
-  const float a = s * __builtin_amdgcn_exp2f((m - mn) * kLog2e);
-  const float b = s2 * __builtin_amdgcn_exp2f((m2 - mn) * kLog2e);
-  s = a + b;
-  m = mn;
-}
-
 }  // namespace hydra
