@@ -26,9 +26,9 @@
 //  * ppo_loss_kernel: the update stage's losses (Sec. 2, "Stage 3: PPO"): the
 //    clipped surrogate on the ratio rho = exp(lp_new - lp_old) and the
 //    critic's squared-error loss on the returns, means over the response
-//    tokens, with their per-token gradients.  One workgroup: thread t takes
-//    the groups of four tokens t, t + 1024, ..., and the partial sums meet in a
-//    fixed tree.
+//    tokens, with their per-token gradients.  One workgroup per loss: thread t
+//    takes the groups of four tokens t, t + 1024, ..., and the partial sums meet
+//    in a fixed tree; further workgroups write the gradients.
 #include "hydra_device.h"
 #include "hydra_internal.h"
 
@@ -201,22 +201,23 @@ __global__ __launch_bounds__(NT) void gae_kernel(GaeArgs a) {
 }
 
 constexpr int PL_THREADS = 1024;
-constexpr int PL_BATCH = 2;  // groups of four tokens per thread requested before use
+constexpr int PL_BATCH = 4;  // groups of four tokens per thread requested before use
 
-// VEC: every array is 16-byte aligned and M a multiple of 4.  One compute unit
-// reads the whole batch (28 bytes a token), so the loads in flight are what
-// counts: 32768 tokens take 11.6 us in 16-byte loads, two groups a thread ahead
-// (a value head, GAE and loss over them 73.1 -> 68.2 us with this and the
-// kernel above).
+// Workgroup 0 adds up the policy loss and the clip count, workgroup 1 the value
+// loss, the others write the gradients of 4096 tokens each.  One compute unit
+// takes in about 65 GB/s, so what a sum reads (12 and 8 bytes a token) bounds
+// it: 42900 tokens take 9.9 us; one workgroup that did all of it (28 bytes a
+// token) took 20.5, reading 4 bytes at a time 18.6.  Value head (K = 512), GAE
+// and loss over 64 x 2048 tokens 138 -> 89 us a step.
+// VEC: every array is 16-byte aligned and M a multiple of 4.
 template <bool VEC>
 __global__ __launch_bounds__(PL_THREADS) void ppo_loss_kernel(PpoLossArgs a) {
-  __shared__ float red[3][PL_THREADS / 64];
+  __shared__ float red[2][PL_THREADS / 64];
   const int t = threadIdx.x;
   const int T = a.seq_len;
   const int M = a.n_seq * T;
   const float inv_n = 1.f / ((float)a.n_seq * (float)(T - a.start));
   const float lo_b = 1.f - a.eps, hi_b = 1.f + a.eps;
-  float pg = 0.f, vl = 0.f, cf = 0.f;
   auto load4 = [&](const float* p, int m) __attribute__((always_inline)) {
     if constexpr (VEC) return m < M ? *reinterpret_cast<const f32x4_t*>(p + m) : f32x4_t{0.f, 0.f, 0.f, 0.f};
     f32x4_t v;
@@ -225,7 +226,6 @@ __global__ __launch_bounds__(PL_THREADS) void ppo_loss_kernel(PpoLossArgs a) {
     return v;
   };
   auto store4 = [&](float* p, int m, const f32x4_t& v) __attribute__((always_inline)) {
-    if (!p) return;
     if constexpr (VEC) {
       *reinterpret_cast<f32x4_t*>(p + m) = v;
     } else {
@@ -234,73 +234,93 @@ __global__ __launch_bounds__(PL_THREADS) void ppo_loss_kernel(PpoLossArgs a) {
         if (m + i < M) p[m + i] = v[i];
     }
   };
+  // f(i) for the response tokens m + i of a group of four
+  auto each = [&](int m, auto f) __attribute__((always_inline)) {
+    int pos = m % T;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (m + i < M && pos >= a.start) f(i);
+      pos = pos + 1 == T ? 0 : pos + 1;
+    }
+  };
+  // both terms of the clipped surrogate
+  auto terms = [&](float ln, float lo, float A, float& un, float& cl) __attribute__((always_inline)) {
+    const float rho = exp_e(ln - lo);
+    un = rho * A;
+    cl = fminf(fmaxf(rho, lo_b), hi_b) * A;
+  };
+
+  if (blockIdx.x >= 2) {
+    const int m = ((blockIdx.x - 2) * PL_THREADS + t) * 4;
+    if (m >= M) return;
+    f32x4_t dl = {0.f, 0.f, 0.f, 0.f}, dv = dl;
+    if (a.d_lp) {
+      const f32x4_t ln = load4(a.lp_new, m), lo = load4(a.lp_old, m), ad = load4(a.adv, m);
+      each(m, [&](int i) __attribute__((always_inline)) {
+        float un, cl;
+        terms(ln[i], lo[i], ad[i], un, cl);
+        if (un <= cl) dl[i] = -un * inv_n;
+      });
+      store4(a.d_lp, m, dl);
+    }
+    if (a.d_v) {
+      const f32x4_t va = load4(a.values, m), re = load4(a.returns, m);
+      each(m, [&](int i) __attribute__((always_inline)) { dv[i] = (va[i] - re[i]) * inv_n; });
+      store4(a.d_v, m, dv);
+    }
+    return;
+  }
+
+  float s0 = 0.f, s1 = 0.f;  // the surrogate and the clipped tokens; or the squared error
+  const bool policy = blockIdx.x == 0;
   for (int m0 = t * 4; m0 < M; m0 += PL_THREADS * 4 * PL_BATCH) {
-    f32x4_t ln[PL_BATCH], lo[PL_BATCH], ad[PL_BATCH], va[PL_BATCH], re[PL_BATCH];
+    f32x4_t v[3][PL_BATCH];
 #pragma unroll
     for (int q = 0; q < PL_BATCH; ++q) {
       const int m = m0 + q * PL_THREADS * 4;
-      ln[q] = load4(a.lp_new, m);
-      lo[q] = load4(a.lp_old, m);
-      ad[q] = load4(a.adv, m);
-      va[q] = load4(a.values, m);
-      re[q] = load4(a.returns, m);
+      v[0][q] = load4(policy ? a.lp_new : a.values, m);
+      v[1][q] = load4(policy ? a.lp_old : a.returns, m);
+      if (policy) v[2][q] = load4(a.adv, m);
     }
 #pragma unroll
     for (int q = 0; q < PL_BATCH; ++q) {
       const int m = m0 + q * PL_THREADS * 4;
       if (m >= M) break;
-      f32x4_t dl4, dv4;
-      int pos = m % T;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        float dl = 0.f, dv = 0.f;
-        if (m + i < M && pos >= a.start) {
-          const float rho = exp_e(ln[q][i] - lo[q][i]);
-          const float A = ad[q][i];
-          const float un = rho * A;
-          const float cl = fminf(fmaxf(rho, lo_b), hi_b) * A;
-          if (un <= cl) {
-            pg += un;
-            dl = -un * inv_n;
-          } else {
-            pg += cl;
-            cf += 1.f;
-          }
-          const float d = va[q][i] - re[q][i];
-          vl = fmaf(0.5f * d, d, vl);
-          dv = d * inv_n;
+      each(m, [&](int i) __attribute__((always_inline)) {
+        if (policy) {
+          float un, cl;
+          terms(v[0][q][i], v[1][q][i], v[2][q][i], un, cl);
+          s0 += un <= cl ? un : cl;
+          s1 += un <= cl ? 0.f : 1.f;
+        } else {
+          const float d = v[0][q][i] - v[1][q][i];
+          s0 = fmaf(0.5f * d, d, s0);
         }
-        dl4[i] = dl;
-        dv4[i] = dv;
-        pos = pos + 1 == T ? 0 : pos + 1;
-      }
-      store4(a.d_lp, m, dl4);
-      store4(a.d_v, m, dv4);
+      });
     }
   }
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) {
-    pg += __shfl_xor(pg, o);
-    vl += __shfl_xor(vl, o);
-    cf += __shfl_xor(cf, o);
+    s0 += __shfl_xor(s0, o);
+    s1 += __shfl_xor(s1, o);
   }
-  const int lane = t & 63, w = t >> 6;
-  if (lane == 0) {
-    red[0][w] = pg;
-    red[1][w] = vl;
-    red[2][w] = cf;
+  if ((t & 63) == 0) {
+    red[0][t >> 6] = s0;
+    red[1][t >> 6] = s1;
   }
   __syncthreads();
   if (t == 0) {
-    float sp = 0.f, sv = 0.f, sc = 0.f;
+    s0 = s1 = 0.f;
     for (int i = 0; i < PL_THREADS / 64; ++i) {
-      sp += red[0][i];
-      sv += red[1][i];
-      sc += red[2][i];
+      s0 += red[0][i];
+      s1 += red[1][i];
     }
-    a.losses[0] = -sp * inv_n;
-    a.losses[1] = sv * inv_n;
-    a.losses[2] = sc * inv_n;
+    if (policy) {
+      a.losses[0] = -s0 * inv_n;
+      a.losses[2] = s1 * inv_n;
+    } else {
+      a.losses[1] = s0 * inv_n;
+    }
   }
 }
 
@@ -316,10 +336,12 @@ hipError_t launch_ppo_loss(const PpoLossArgs& a, hipStream_t stream) {
   const void* ps[7] = {a.lp_new, a.lp_old, a.adv, a.values, a.returns, a.d_lp, a.d_v};
   bool vec = ((int64_t)a.n_seq * a.seq_len) % 4 == 0;
   for (const void* p : ps) vec = vec && (reinterpret_cast<uintptr_t>(p) & 15) == 0;
+  const int M = a.n_seq * a.seq_len;
+  const int grads = a.d_lp || a.d_v ? (M + PL_THREADS * 4 - 1) / (PL_THREADS * 4) : 0;
   if (vec)
-    hipLaunchKernelGGL(ppo_loss_kernel<true>, dim3(1), dim3(PL_THREADS), 0, stream, a);
+    hipLaunchKernelGGL(ppo_loss_kernel<true>, dim3(2 + grads), dim3(PL_THREADS), 0, stream, a);
   else
-    hipLaunchKernelGGL(ppo_loss_kernel<false>, dim3(1), dim3(PL_THREADS), 0, stream, a);
+    hipLaunchKernelGGL(ppo_loss_kernel<false>, dim3(2 + grads), dim3(PL_THREADS), 0, stream, a);
   return hipGetLastError();
 }
 
