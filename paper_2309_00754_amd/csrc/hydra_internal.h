@@ -76,7 +76,9 @@ struct TpreArgs {
   float* part;        // [kTpreMaxChunks x M x RP] fp32 partial sums over K chunks
   uint16_t* tT;       // [2][RP][Mp] bf16 hi and lo planes of (s T)^T, rows M..Mp zero, or nullptr
   int Mp;             // leading dimension of tT (M rounded up to 32)
-  int Kform;          // the K that the choice of kernel looks at (0: K; jobs that may or may not run together share it)
+  // jobs that may or may not run together: the longest K and the sum of K over
+  // both, which the choice of kernel and chunks looks at (0: K)
+  int Kform, Kall;
 };
 // K is split into at most kTpreMaxChunks chunks of at least 1024, so that
 // the pre-pass spreads over many workgroups; the partial products are then

@@ -384,6 +384,7 @@ hipError_t launch_lora_backward(const BackwardArgs& a, void* ws, hipStream_t str
   u.K = a.N;
   u.r = a.r;
   u.Kform = tt.Kform = std::max(a.N, a.K);
+  u.Kall = tt.Kall = a.N + a.K;
   u.ts = a.dx ? reinterpret_cast<uint16_t*>(w + l.tsu) : nullptr;
   u.part = reinterpret_cast<float*>(w + l.tpart);
   u.tT = a.dA ? reinterpret_cast<uint16_t*>(w + l.uT) : nullptr;

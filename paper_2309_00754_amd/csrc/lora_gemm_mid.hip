@@ -635,26 +635,45 @@ hipError_t launch_t_part_mid(const TpreArgs* as, int n, int rp, int* nkc, hipStr
   g.ga.N = rp;
   g.ga.r = as[0].r;
   g.vec4 = 1;  // rows of rp fp32 in a 16-byte aligned workspace
-  // 64 x 64 tiles and as many K chunks (up to 8, each of at least 256) as give
-  // at most 256 workgroups; 128 x 128 tiles where those would not fit one round
-  // unsplit.  Whole linear with pre-pass, us: M = 4096, K = N = 2048, rank 128
-  // 56.3 with 2 chunks, 60.6 with 4, 69 with 8, 61.6 for 128 x 128 in 8 chunks;
-  // 3000 x 4096 x 4096, rank 64 126 with 4 chunks against 130; 1024 x 4096 x
-  // 4096, rank 128 63.3 with 8 chunks against 64.0 with 4.  Tile and chunks
-  // depend on M, K and rp alone, so that T has the same bits in every group.
-  const int rows64 = (as[0].M + 63) / 64 * (rp / 64);
-  const int tile = rp == 128 && rows64 > 256 ? 4 : 2;
-  const int tiles = tile == 4 ? (as[0].M + 127) / 128 : rows64;
-  const int most = tiles >= 256 ? 1 : 256 / tiles < kTpreMaxChunks ? 256 / tiles : kTpreMaxChunks;
+  // Tile (64 x 64, at rank 128 also 128 x 128) and chunk length by the model of
+  // kMidTiles, plus the partial sums written and read again at 5 TB/s.  Whole
+  // linear with pre-pass, us: M = 4096, K = N = 2048, rank 128 56.3 with 2
+  // chunks, 60.6 with 4, 69 with 8, 61.6 for 128 x 128 in 8 chunks; 3000 x 4096
+  // x 4096, rank 64 126 with 4 chunks against 130; 1024 x 4096 x 4096, rank 128
+  // 63.3 with 8 chunks against 64.0 with 4.  The backward's two jobs share a
+  // launch and count together: 2900 rows of 8192 and 2048 values, rank 128, 193 us
+  // a backward call against 214 with each counted alone.  Tile and length depend
+  // on M, Kform, Kall and rp alone, so that T has the same bits in every group.
+  const int M = as[0].M;
+  const int klong = as[0].Kform > 0 ? as[0].Kform : as[0].K;
+  const int kshort = as[0].Kall > 0 ? as[0].Kall - klong : 0;
+  int tile = 2, len = 0;
+  float cost = 0.f;
+  for (int i = 2; i <= (rp == 128 ? 4 : 2); i += 2) {
+    const MidTile& c = kMidTiles[i];
+    const int64_t tiles = (int64_t)((M + c.tm - 1) / c.tm) * ((rp + c.tn - 1) / c.tn);
+    for (int n_long = 1; n_long <= kTpreMaxChunks; ++n_long) {
+      const int l = ((klong + n_long - 1) / n_long + 127) / 128 * 128;
+      if (n_long > 1 && l < 256) break;
+      const int64_t chunks = (klong + l - 1) / l + (kshort + l - 1) / l;
+      const float t = c.base + (float)((tiles * chunks + 255) / 256) * (c.fixed + (float)(l / 64) * c.step) +
+                      (float)(chunks * M * rp) * 8.f / 5e6f;
+      if (len == 0 || t < cost) {
+        cost = t;
+        tile = i;
+        len = l;
+      }
+    }
+  }
   for (int j = 0; j < n; ++j) {
     if (as[j].M != as[0].M || as[j].r != as[0].r) return hipErrorInvalidValue;
     g.ga.x[j] = as[j].x;
     g.ga.W[j] = as[j].A;
     g.ga.y_off[j] = as[j].part;
     g.kall[j] = as[j].K;
-    const int want = (as[j].K + 255) / 256 < most ? (as[j].K + 255) / 256 : most;
-    g.kch[j] = ((as[j].K + want - 1) / want + 63) / 64 * 64;
-    nkc[j] = g.nkc[j] = (as[j].K + g.kch[j] - 1) / g.kch[j];
+    g.kch[j] = len;
+    nkc[j] = g.nkc[j] = (as[j].K + len - 1) / len;
+    if (nkc[j] > kTpreMaxChunks) return hipErrorInvalidValue;
   }
   return launch_any(g, 0, tile, stream);
 }

@@ -217,11 +217,13 @@ __global__ __launch_bounds__(S_WAVES * 64) void lora_t_small_kernel(TpreJobs job
 // Where the one launch is faster than partial sums + finish (and the gap of
 // about 1.5 us between them), us at M = 1024: rank 16, K = 2048 7.0 against 4.6
 // + 4.1, K = 4096 9.7 against 4.8 + 5.0, K = 8192 16.7 against 6.0 + 4.9; rank
-// 128, K = 2048 9.9 against 5.8 + 4.8 (M = 2048: 18.1 against 7 + 5: two rounds
-// of workgroups).
-bool use_small(int M, int K, int rp) {
-  if (rp <= 32) return K <= 4096;
-  return K <= 2048 && (int64_t)M * rp <= 1024 * 128;
+// 128, K = 2048 9.9 against 5.8 + 4.8.  Only while its workgroups are at most
+// 256, one round (M = 2048, rank 128: 18.1 against 7 + 5; the backward's two
+// jobs at M = 2510, K = 4096, rank 16: 16.9 against 11.4 + 4.8).
+bool use_small(const TpreArgs& a, int rp) {
+  const int K = a.Kform > 0 ? a.Kform : a.K;
+  const int64_t groups = (int64_t)((a.M + 15) / 16) * (rp / 16 / small_jt(rp)) * (a.Kall > 0 ? 2 : 1);
+  return K <= (rp <= 32 ? 4096 : 2048) && groups <= 256;
 }
 
 // Workgroups [bbeg[j], bbeg[j + 1]) finish job j; those past the last job's
@@ -252,7 +254,7 @@ hipError_t launch_rp(const TpreArgs* as, int n, const uint16_t** bp_used, hipStr
   const int M = a0.M;  // (every job has the same rows)
   const size_t pads = ((size_t)a0.N * RP + 255) / 256;
   const int pad_blocks = direct ? 0 : (int)(pads < 2048 ? pads : 2048);
-  if (use_small(M, a0.Kform > 0 ? a0.Kform : a0.K, RP)) {
+  if (use_small(a0, RP)) {
     for (int j = 0; j < n; ++j) {
       jobs.a[j] = as[j];
       jobs.bbeg[j + 1] = jobs.bbeg[j] + ((as[j].tT ? as[j].Mp : M) + 15) / 16 * (RP / 16 / small_jt(RP));
