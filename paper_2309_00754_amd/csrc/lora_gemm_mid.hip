@@ -23,11 +23,20 @@
 //    workspace.
 // The K order of every output depends on the tile shape alone, and the shape
 // on M, N and K alone, so an output has the same bits whatever the entry point.
+#include <algorithm>
+
 #include "hydra_device.h"
 #include "hydra_internal.h"
 
 namespace hydra {
 namespace {
+
+// Up to kFewRows rows only tiles of at most kFewTileMax outputs serve, and the
+// sums run in short chains: a decode step's outputs keep the error that sums
+// spread over many waves give.
+constexpr int kFewRows = 16;
+constexpr int kFewTileMax = 64 * 64;
+constexpr int kFoldSlabs = 4;
 
 struct MidArgs {
   GroupArgs ga;                   // the members' operands; A null: no adapter
@@ -38,6 +47,7 @@ struct MidArgs {
   int kch[kMaxGroup];
   int nkc[kMaxGroup];
   int ntm, ntn;                   // tiles of one member
+  int total;                      // workgroups with a tile (the grid may hold a few more)
   int vec4;                       // outputs may be written with 16-byte stores
 };
 
@@ -92,6 +102,7 @@ struct GemmMid {
   static_assert(NS >= 2 && (SPW == 1 || SPW % 2 == 0), "ring and k-steps");
   static_assert(LDS <= kLds, "fits in LDS");
   static_assert(NU % KS == 0, "the reduce-scatter ends with whole units");
+  static_assert(RA == 0 || TM * TN > kFewTileMax || NP == 3, "every bit of s T on the tiles that serve few rows");
   static_assert(RA == 0 || TPW * NWN * TSPLIT * 16 == WM, "T rows split over the waves of a row block");
 };
 
@@ -106,7 +117,8 @@ struct IC {
 // partial sums [chunk][M][N].
 enum MidMode { PLAIN, PRE, PART };
 
-template <class G, MidMode MODE>
+// FOLD: see the main loop.
+template <class G, MidMode MODE, bool FOLD>
 __global__ __launch_bounds__(G::NT, G::NT / 256) void lora_gemm_mid_kernel(MidArgs g) {
   constexpr int TM = G::TM, TN = G::TN, WM = G::WM, WN = G::WN, KS = G::KS, BK = G::BK, RA = G::RA;
   constexpr int NW = G::NW, NT = G::NT, MT = G::MT, NTL = G::NTL, NQ = G::NQ, CPR = G::CPR, RPB = G::RPB;
@@ -129,7 +141,8 @@ __global__ __launch_bounds__(G::NT, G::NT / 256) void lora_gemm_mid_kernel(MidAr
   // on one L2).
   int gi, tmi, tni, kc = 0;
   {
-    const int tiles = g.ntm * g.ntn, total = gridDim.x, bid = blockIdx.x;
+    const int tiles = g.ntm * g.ntn, total = g.total, bid = blockIdx.y * gridDim.x + blockIdx.x;
+    if (bid >= total) return;  // (the whole workgroup, before any barrier)
     const int q = total >> 3, rem = total & 7, xcd = bid & 7;
     int lid = xcd * q + min(xcd, rem) + (bid >> 3);
     gi = lid / tiles;
@@ -310,14 +323,47 @@ __global__ __launch_bounds__(G::NT, G::NT / 256) void lora_gemm_mid_kernel(MidAr
     for (int r = 0; r < NRT; ++r) read_t(0, r);
     mfma_t();
   }
-  // the slabs, unrolled over the ring 
+  // The slabs, unrolled over the ring.  FOLD (up to 16 rows and more than
+  // kFoldSlabs slabs): the sums of every kFoldSlabs slabs go to a total, so that
+  // no chain of additions has K / (16 KS) links.  Error of y_off and y_on (rank
+  // 8) against 64 bits at K = 4096: 1.9e-7 and 1.9e-7 in one chain, 0.9e-7 and
+  // 1.0e-7 so; the kernel of 16 waves that served these rows had 1.2e-7 and
+  // 1.3e-7.  (Counted in slabs and not
+  // in passes over the ring, whose stages depend on the rank: y_off has the same
+  // bits at every rank.)
+  f32x16_t tot[FOLD ? MT : 1][FOLD ? NTL : 1];
+  f32x4_t totT[FOLD ? TPW : 1][TJ1];
+  if constexpr (FOLD) {
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) tot[q / NTL][q % NTL] = acc[q / NTL][q % NTL];
+#pragma unroll
+    for (int q = 0; q < TPW * TJ; ++q) totT[q / TJ1][q % TJ1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  }
+  auto fold = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        tot[q / NTL][q % NTL][e] += acc[q / NTL][q % NTL][e];
+        acc[q / NTL][q % NTL][e] = 0.f;
+      }
+#pragma unroll
+    for (int q = 0; q < TPW * TJ; ++q) {
+      totT[q / TJ1][q % TJ1] += accT[q / TJ1][q % TJ1];
+      accT[q / TJ1][q % TJ1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    }
+  };
   constexpr int PS = SPW == 1 ? 1 : 0;
   constexpr int UN = NS;
   static_assert(UN <= 8, "slabs listed below");
   for (int kt = 0; kt < nkt; kt += UN) {
 #define HYDRA_MID_SLAB(u)                 \
   if constexpr ((u) < UN)                 \
-    if ((u) == 0 || kt + (u) < nkt) slab(IC<(u) % NS>{}, IC<((u) & PS)>{}, kt + (u));
+    if ((u) == 0 || kt + (u) < nkt) {     \
+      slab(IC<(u) % NS>{}, IC<((u) & PS)>{}, kt + (u)); \
+      if constexpr (FOLD)                 \
+        if ((kt + (u) + 1) % kFoldSlabs == 0) fold(); \
+    }
     HYDRA_MID_SLAB(0)
     HYDRA_MID_SLAB(1)
     HYDRA_MID_SLAB(2)
@@ -327,6 +373,14 @@ __global__ __launch_bounds__(G::NT, G::NT / 256) void lora_gemm_mid_kernel(MidAr
     HYDRA_MID_SLAB(6)
     HYDRA_MID_SLAB(7)
 #undef HYDRA_MID_SLAB
+  }
+  if constexpr (FOLD) {
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[q / NTL][q % NTL][e] += tot[q / NTL][q % NTL][e];
+#pragma unroll
+    for (int q = 0; q < TPW * TJ; ++q) accT[q / TJ1][q % TJ1] += totT[q / TJ1][q % TJ1];
   }
   mid_barrier<0>();  // every copy has landed, every wave is done with the ring
 
@@ -392,7 +446,7 @@ __global__ __launch_bounds__(G::NT, G::NT / 256) void lora_gemm_mid_kernel(MidAr
       for (int p = 0; p < NP; ++p) {
         const uint32_t part = f32_to_bf16_rne(v);
         Ts[(row * NP + p) * RA + j] = (uint16_t)part;
-        v -= bf16_to_f32(part);
+        v = (part & 0x7FFF) < 0x7F80 ? v - bf16_to_f32(part) : 0.f;  // (an infinity has no rounding error)
       }
     }
     __syncthreads();
@@ -529,9 +583,10 @@ __global__ __launch_bounds__(G::NT, G::NT / 256) void lora_gemm_mid_kernel(MidAr
 // are fits to kernel times over M = 17 ... 4096 and eight (K, N) from 700 to
 // 11008 at rank 16 (rms error 11-18%; the model's choice is 0.4% slower than
 // the best one on average, 16% at most, and never slower than the 128 x 256
-// tile by more than 1.2%).  What they say: a 64-wide slab of a tile costs its
-// bytes at 45 B/clk for the smallest tiles to 60 B/clk for the largest, so a
-// larger tile is cheaper per output as long as it still gives 256 tiles.
+// tile by more than 1.2% there; 1100 x 4096 x 4096 and 2100 x 2048 x 8192 are,
+// by 4% and 2%).  What they say: a 64-wide slab of a tile costs its bytes at 66
+// to 74 GB/s per CU whatever the tile, so a larger one is cheaper per output as
+// long as it still gives 256 tiles.
 // M x K x N, us: 48 x 4096 x 4096 41.4 -> 11.6, 333 x 4096 x 11008 72 -> 58,
 // 512 x 4096 x 4096 47.6 -> 29.9, 1000 x 11008 x 4096 157 -> 121, 500 x 2048 x
 // 2048 30.2 -> 13.6 (128 x 256 tile -> here, rank 16).  Rows 9 to 16, against
@@ -553,7 +608,7 @@ float tile_cost(const MidTile& c, int M, int N, int K) {
   return c.base + (float)((tiles + 255) / 256) * (c.fixed + (float)((K + 63) / 64) * c.step);
 }
 
-template <class G, MidMode MODE>
+template <class G, MidMode MODE, bool FOLD = false>
 void launch_tile(MidArgs& g, hipStream_t stream) {
   int members = g.ga.G;  // (member, chunk) pairs of the pre-pass
   if constexpr (MODE == PART) {
@@ -562,7 +617,18 @@ void launch_tile(MidArgs& g, hipStream_t stream) {
   }
   g.ntm = (g.ga.M + G::TM - 1) / G::TM;
   g.ntn = (g.ga.N + G::TN - 1) / G::TN;
-  hipLaunchKernelGGL((lora_gemm_mid_kernel<G, MODE>), dim3(g.ntm * g.ntn * members), dim3(G::NT), 0, stream, g);
+  // a dispatch counts the work-items of a dimension in 32 bits: the largest
+  // grids are split over y
+  g.total = g.ntm * g.ntn * members;
+  const int gx = std::min(g.total, 1 << 22);
+  hipLaunchKernelGGL((lora_gemm_mid_kernel<G, MODE, FOLD>), dim3(gx, (g.total + gx - 1) / gx), dim3(G::NT), 0, stream, g);
+}
+
+template <class G>
+void launch_plain(MidArgs& g, hipStream_t stream) {
+  if constexpr (G::TM * G::TN <= kFewTileMax)
+    if (g.ga.M <= kFewRows && g.ga.K > kFoldSlabs * G::BK) return launch_tile<G, PLAIN, true>(g, stream);
+  launch_tile<G, PLAIN>(g, stream);
 }
 
 template <int TM, int TN, int WM, int WN, int KS, int BK, int NS>
@@ -572,13 +638,13 @@ hipError_t launch_mid(MidArgs& g, int ra, hipStream_t stream) {
   else if (g.rp > 0)
     launch_tile<GemmMid<TM, TN, WM, WN, KS, BK, NS, 0>, PRE>(g, stream);
   else if (ra == 0)
-    launch_tile<GemmMid<TM, TN, WM, WN, KS, BK, NS, 0>, PLAIN>(g, stream);
+    launch_plain<GemmMid<TM, TN, WM, WN, KS, BK, NS, 0>>(g, stream);
   else if (ra == 16)
-    launch_tile<GemmMid<TM, TN, WM, WN, KS, BK, NS, 16>, PLAIN>(g, stream);
+    launch_plain<GemmMid<TM, TN, WM, WN, KS, BK, NS, 16>>(g, stream);
   else if (ra == 32)
-    launch_tile<GemmMid<TM, TN, WM, WN, KS, BK, NS, 32>, PLAIN>(g, stream);
+    launch_plain<GemmMid<TM, TN, WM, WN, KS, BK, NS, 32>>(g, stream);
   else if (ra == 64)
-    launch_tile<GemmMid<TM, TN, WM, WN, KS, BK, NS, 64>, PLAIN>(g, stream);
+    launch_plain<GemmMid<TM, TN, WM, WN, KS, BK, NS, 64>>(g, stream);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();
@@ -599,9 +665,13 @@ hipError_t launch_any(MidArgs& g, int ra, int tile, hipStream_t stream) {
 }  // namespace
 
 int gemm_mid_tile(int M, int N, int K) {
-  int best = -1;
-  float cost = tile_cost(kBigTile, M, N, K);
+  // Up to 16 rows always one of the tiles up to 64 x 64: they carry s T in all
+  // its 24 bits (128 x 192 holds two bf16 parts of it) and sum in short chains.
+  const bool few = M <= kFewRows;
+  int best = few ? 0 : -1;
+  float cost = tile_cost(few ? kMidTiles[0] : kBigTile, M, N, K);
   for (int i = 0; i < kMidTileCount; ++i) {
+    if (few && kMidTiles[i].tm * kMidTiles[i].tn > kFewTileMax) break;
     const float c = tile_cost(kMidTiles[i], M, N, K);
     if (c < cost) {
       cost = c;

@@ -1,4 +1,4 @@
-"""The dual GEMM's smaller tiles (17 rows to a few hundred): edges of every tile, K shorter than a slab and longer than
+"""The dual GEMM's smaller tiles (9 rows to a few hundred): edges of every tile, K shorter than a slab and longer than
 the ring, every way the LoRA update reaches them, against the float64 oracle; and the bits that the entry points share.
 Tolerances: the arithmetic bound of the other linear tests (2e-4 relative)."""
 import numpy as np
@@ -95,3 +95,38 @@ def test_mid_group_members_have_the_bits_of_single_calls(M, N, K, r, dev):
     for i in range(G):
         assert torch.equal(offs[i], ons[i])
         assert np.isfinite(host(offs[i])).all()
+
+
+@pytest.mark.parametrize("M,N,K,r", [(9, 50001, 72, 16), (16, 52000, 64, 64), (12, 300, 264, 8), (16, 11008, 1032, 64),
+                                     (9, 700, 2056, 20), (16, 512, 520, 16)])
+def test_few_rows_keep_the_bits_of_t(M, N, K, r, dev):
+    """Up to 16 rows, s T holds 24 bits at every width, and no sum is one long chain.  In 2-norm y_on is then off 64 bits
+    by the rounding of fp32 sums: under 2^-24 for each of at most 70 additions in a row adding up at random, 5e-7 (and
+    under sqrt(K + r) 2^-24 where there are fewer products).  With s T in two bf16 parts it would be off by 2e-6."""
+    import torch
+    say("few rows", M, N, K, r)
+    c, x, W, A, B = _inputs(M, N, K, r, dev)
+    e_on = lora_linear_ref(c.x, c.W, c.A, c.B, c.s)[1]
+    y_on = _nan(M, N, dev)
+    H.hydra_lora_linear(x, W, A, B, c.s, None, y_on)
+    torch.cuda.synchronize()
+    err = np.linalg.norm(host(y_on) - e_on) / np.linalg.norm(e_on)
+    assert err < min(5e-7, np.sqrt(K + r) * 2.0 ** -24), err
+    y_off, alone = _nan(M, N, dev), _nan(M, N, dev)  # y_off has the same bits with and without an adapter
+    H.hydra_lora_linear(x, W, A, B, c.s, y_off, y_on)
+    H.hydra_lora_linear(x, W, None, None, 0.0, alone, None)
+    torch.cuda.synchronize()
+    assert torch.equal(y_off, alone)
+
+
+def test_an_infinite_t_gives_infinite_outputs(dev):
+    import torch
+    say("infinite t")
+    M, N, K, r = 12, 40, 64, 16
+    x, W, A, B = (torch.ones(s, device=dev, dtype=torch.bfloat16) for s in ((M, K), (N, K), (r, K), (N, r)))
+    A[3] = 3e38  # the sum of 64 of them overflows
+    B[::2, 3] = -1
+    y_on = _nan(M, N, dev)
+    H.hydra_lora_linear(x, W, A, B, 2.0, None, y_on)
+    torch.cuda.synchronize()
+    assert (y_on[:, ::2] == float("-inf")).all() and (y_on[:, 1::2] == float("inf")).all()
