@@ -464,7 +464,7 @@ def bench_single_linear(torch, H, WL, dev, iters=200):
     fl = lin_flops(c.M, c.K, c.N, c.r)
     return dict(M=c.M, K=c.K, N=c.N, r=c.r, us_graph=round(graph, 2), us_eager=round(eager, 2),
                 tflops_graph=round(fl / graph / 1e6, 3),
-                note="one call = one launch of the small-M MFMA kernel (8 < M <= 16); median of 5 blocks of 200 "
+                note="one call = one launch of the GEMM on its smallest tiles (8 < M <= 16); median of 5 blocks of 200 "
                      "calls, eager (host-bound) and replayed from one captured HIP graph")
 
 
