@@ -47,7 +47,7 @@ struct MidArgs {
   int kch[kMaxGroup];
   int nkc[kMaxGroup];
   int ntm, ntn;                   // tiles of one member
-  int total;                      // workgroups with a tile (the grid may hold a few more)
+  int total, first;               // workgroups in all, and of the launches before this one
   int vec4;                       // outputs may be written with 16-byte stores
 };
 
@@ -141,8 +141,7 @@ __global__ __launch_bounds__(G::NT, G::NT / 256) void lora_gemm_mid_kernel(MidAr
   // on one L2).
   int gi, tmi, tni, kc = 0;
   {
-    const int tiles = g.ntm * g.ntn, total = g.total, bid = blockIdx.y * gridDim.x + blockIdx.x;
-    if (bid >= total) return;  // (the whole workgroup, before any barrier)
+    const int tiles = g.ntm * g.ntn, total = g.total, bid = g.first + blockIdx.x;
     const int q = total >> 3, rem = total & 7, xcd = bid & 7;
     int lid = xcd * q + min(xcd, rem) + (bid >> 3);
     gi = lid / tiles;
@@ -328,9 +327,8 @@ __global__ __launch_bounds__(G::NT, G::NT / 256) void lora_gemm_mid_kernel(MidAr
   // no chain of additions has K / (16 KS) links.  Error of y_off and y_on (rank
   // 8) against 64 bits at K = 4096: 1.9e-7 and 1.9e-7 in one chain, 0.9e-7 and
   // 1.0e-7 so; the kernel of 16 waves that served these rows had 1.2e-7 and
-  // 1.3e-7.  (Counted in slabs and not
-  // in passes over the ring, whose stages depend on the rank: y_off has the same
-  // bits at every rank.)
+  // 1.3e-7.  (Counted in slabs and not in passes over the ring, whose stages
+  // depend on the rank: y_off has the same bits at every rank.)
   f32x16_t tot[FOLD ? MT : 1][FOLD ? NTL : 1];
   f32x4_t totT[FOLD ? TPW : 1][TJ1];
   if constexpr (FOLD) {
@@ -618,10 +616,13 @@ void launch_tile(MidArgs& g, hipStream_t stream) {
   g.ntm = (g.ga.M + G::TM - 1) / G::TM;
   g.ntn = (g.ga.N + G::TN - 1) / G::TN;
   // a dispatch counts the work-items of a dimension in 32 bits: the largest
-  // grids are split over y
+  // grids take several launches (of a multiple of 8 workgroups: the XCD of a
+  // workgroup follows from its number).  A second grid dimension with a test for
+  // the surplus workgroups cost every call: 16 x 512 x 512 4.96 -> 5.21 us.
   g.total = g.ntm * g.ntn * members;
-  const int gx = std::min(g.total, 1 << 22);
-  hipLaunchKernelGGL((lora_gemm_mid_kernel<G, MODE, FOLD>), dim3(gx, (g.total + gx - 1) / gx), dim3(G::NT), 0, stream, g);
+  for (g.first = 0; g.first < g.total; g.first += 1 << 22)
+    hipLaunchKernelGGL((lora_gemm_mid_kernel<G, MODE, FOLD>), dim3(std::min(g.total - g.first, 1 << 22)), dim3(G::NT), 0,
+                       stream, g);
 }
 
 template <class G>
