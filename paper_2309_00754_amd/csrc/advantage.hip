@@ -209,38 +209,55 @@ constexpr int PL_BATCH = 4;  // groups of four tokens per thread requested befor
 // it: 42900 tokens take 9.9 us; one workgroup that did all of it (28 bytes a
 // token) took 20.5, reading 4 bytes at a time 18.6.  Value head (K = 512), GAE
 // and loss over 64 x 2048 tokens 138 -> 89 us a step.
-// VEC: every array is 16-byte aligned and M a multiple of 4.
+// VEC: every array is 16-byte aligned.  A thread's group of four tokens is then
+// 4 t .. 4 t + 3 of a block of 4096 in one load per array, and the M % 4 tokens
+// left over are taken one by one; else tokens t, t + 1024, ... of the block, so
+// that the lanes of a 4-byte load stay side by side (46 x 1659 tokens, four
+// neighbouring tokens a thread in 4-byte loads 53.8 us, so 18.5, VEC 13.9).
 template <bool VEC>
 __global__ __launch_bounds__(PL_THREADS) void ppo_loss_kernel(PpoLossArgs a) {
   __shared__ float red[2][PL_THREADS / 64];
+  constexpr int BLOCK = PL_THREADS * 4;
   const int t = threadIdx.x;
   const int T = a.seq_len;
   const int M = a.n_seq * T;
+  const int Mv = VEC ? M & ~3 : M;  // tokens taken in groups
   const float inv_n = 1.f / ((float)a.n_seq * (float)(T - a.start));
   const float lo_b = 1.f - a.eps, hi_b = 1.f + a.eps;
-  auto load4 = [&](const float* p, int m) __attribute__((always_inline)) {
-    if constexpr (VEC) return m < M ? *reinterpret_cast<const f32x4_t*>(p + m) : f32x4_t{0.f, 0.f, 0.f, 0.f};
-    f32x4_t v;
+  // token i of this thread's group in the block from b on
+  auto token = [&](int b, int i) __attribute__((always_inline)) { return VEC ? b + 4 * t + i : b + t + i * PL_THREADS; };
+  auto load4 = [&](const float* p, int b) __attribute__((always_inline)) {
+    f32x4_t v = {0.f, 0.f, 0.f, 0.f};
+    if constexpr (VEC) {
+      if (token(b, 0) < Mv) v = *reinterpret_cast<const f32x4_t*>(p + token(b, 0));
+    } else {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) v[i] = m + i < M ? p[m + i] : 0.f;
+      for (int i = 0; i < 4; ++i) v[i] = token(b, i) < Mv ? p[token(b, i)] : 0.f;
+    }
     return v;
   };
-  auto store4 = [&](float* p, int m, const f32x4_t& v) __attribute__((always_inline)) {
+  auto store4 = [&](float* p, int b, const f32x4_t& v) __attribute__((always_inline)) {
     if constexpr (VEC) {
-      *reinterpret_cast<f32x4_t*>(p + m) = v;
+      if (token(b, 0) < Mv) *reinterpret_cast<f32x4_t*>(p + token(b, 0)) = v;
     } else {
 #pragma unroll
       for (int i = 0; i < 4; ++i)
-        if (m + i < M) p[m + i] = v[i];
+        if (token(b, i) < Mv) p[token(b, i)] = v[i];
     }
   };
-  // f(i) for the response tokens m + i of a group of four
-  auto each = [&](int m, auto f) __attribute__((always_inline)) {
-    int pos = m % T;
+  const int stride_pos = PL_THREADS % T;
+  // f(i) for the response tokens of this thread's group
+  auto each = [&](int b, auto f) __attribute__((always_inline)) {
+    int pos = token(b, 0) % T;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      if (m + i < M && pos >= a.start) f(i);
-      pos = pos + 1 == T ? 0 : pos + 1;
+      if (token(b, i) < Mv && pos >= a.start) f(i);
+      if constexpr (VEC) {
+        pos = pos + 1 == T ? 0 : pos + 1;
+      } else {
+        pos += stride_pos;
+        pos = pos >= T ? pos - T : pos;
+      }
     }
   };
   // both terms of the clipped surrogate
@@ -249,56 +266,71 @@ __global__ __launch_bounds__(PL_THREADS) void ppo_loss_kernel(PpoLossArgs a) {
     un = rho * A;
     cl = fminf(fmaxf(rho, lo_b), hi_b) * A;
   };
+  auto d_policy = [&](float ln, float lo, float A) __attribute__((always_inline)) {
+    float un, cl;
+    terms(ln, lo, A, un, cl);
+    return un <= cl ? -un * inv_n : 0.f;
+  };
+
+  const bool left = VEC && Mv < M && t < M - Mv;  // this thread takes the left-over token Mv + t
+  auto is_response = [&](int m) __attribute__((always_inline)) { return m % T >= a.start; };
 
   if (blockIdx.x >= 2) {
-    const int m = ((blockIdx.x - 2) * PL_THREADS + t) * 4;
-    if (m >= M) return;
-    f32x4_t dl = {0.f, 0.f, 0.f, 0.f}, dv = dl;
+    const int b = (blockIdx.x - 2) * BLOCK;
+    if (left && blockIdx.x == gridDim.x - 1) {
+      const int m = Mv + t;
+      const bool on = is_response(m);
+      if (a.d_lp) a.d_lp[m] = on ? d_policy(a.lp_new[m], a.lp_old[m], a.adv[m]) : 0.f;
+      if (a.d_v) a.d_v[m] = on ? (a.values[m] - a.returns[m]) * inv_n : 0.f;
+    }
+    if (token(b, 0) >= Mv) return;
     if (a.d_lp) {
-      const f32x4_t ln = load4(a.lp_new, m), lo = load4(a.lp_old, m), ad = load4(a.adv, m);
-      each(m, [&](int i) __attribute__((always_inline)) {
-        float un, cl;
-        terms(ln[i], lo[i], ad[i], un, cl);
-        if (un <= cl) dl[i] = -un * inv_n;
-      });
-      store4(a.d_lp, m, dl);
+      f32x4_t dl = {0.f, 0.f, 0.f, 0.f};
+      const f32x4_t ln = load4(a.lp_new, b), lo = load4(a.lp_old, b), ad = load4(a.adv, b);
+      each(b, [&](int i) __attribute__((always_inline)) { dl[i] = d_policy(ln[i], lo[i], ad[i]); });
+      store4(a.d_lp, b, dl);
     }
     if (a.d_v) {
-      const f32x4_t va = load4(a.values, m), re = load4(a.returns, m);
-      each(m, [&](int i) __attribute__((always_inline)) { dv[i] = (va[i] - re[i]) * inv_n; });
-      store4(a.d_v, m, dv);
+      f32x4_t dv = {0.f, 0.f, 0.f, 0.f};
+      const f32x4_t va = load4(a.values, b), re = load4(a.returns, b);
+      each(b, [&](int i) __attribute__((always_inline)) { dv[i] = (va[i] - re[i]) * inv_n; });
+      store4(a.d_v, b, dv);
     }
     return;
   }
 
   float s0 = 0.f, s1 = 0.f;  // the surrogate and the clipped tokens; or the squared error
   const bool policy = blockIdx.x == 0;
-  for (int m0 = t * 4; m0 < M; m0 += PL_THREADS * 4 * PL_BATCH) {
+  auto add = [&](float x, float y, float z) __attribute__((always_inline)) {
+    if (policy) {
+      float un, cl;
+      terms(x, y, z, un, cl);
+      s0 += un <= cl ? un : cl;
+      s1 += un <= cl ? 0.f : 1.f;
+    } else {
+      const float d = x - y;
+      s0 = fmaf(0.5f * d, d, s0);
+    }
+  };
+  const float* const p0 = policy ? a.lp_new : a.values;
+  const float* const p1 = policy ? a.lp_old : a.returns;
+  for (int b0 = 0; token(b0, 0) < Mv; b0 += BLOCK * PL_BATCH) {
     f32x4_t v[3][PL_BATCH];
 #pragma unroll
     for (int q = 0; q < PL_BATCH; ++q) {
-      const int m = m0 + q * PL_THREADS * 4;
-      v[0][q] = load4(policy ? a.lp_new : a.values, m);
-      v[1][q] = load4(policy ? a.lp_old : a.returns, m);
-      if (policy) v[2][q] = load4(a.adv, m);
+      const int b = b0 + q * BLOCK;
+      v[0][q] = load4(p0, b);
+      v[1][q] = load4(p1, b);
+      if (policy) v[2][q] = load4(a.adv, b);
     }
 #pragma unroll
     for (int q = 0; q < PL_BATCH; ++q) {
-      const int m = m0 + q * PL_THREADS * 4;
-      if (m >= M) break;
-      each(m, [&](int i) __attribute__((always_inline)) {
-        if (policy) {
-          float un, cl;
-          terms(v[0][q][i], v[1][q][i], v[2][q][i], un, cl);
-          s0 += un <= cl ? un : cl;
-          s1 += un <= cl ? 0.f : 1.f;
-        } else {
-          const float d = v[0][q][i] - v[1][q][i];
-          s0 = fmaf(0.5f * d, d, s0);
-        }
-      });
+      const int b = b0 + q * BLOCK;
+      if (token(b, 0) >= Mv) break;
+      each(b, [&](int i) __attribute__((always_inline)) { add(v[0][q][i], v[1][q][i], policy ? v[2][q][i] : 0.f); });
     }
   }
+  if (left && is_response(Mv + t)) add(p0[Mv + t], p1[Mv + t], policy ? a.adv[Mv + t] : 0.f);
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) {
     s0 += __shfl_xor(s0, o);
@@ -334,7 +366,7 @@ hipError_t launch_value_head(const ValueHeadArgs& a, hipStream_t stream) {
 
 hipError_t launch_ppo_loss(const PpoLossArgs& a, hipStream_t stream) {
   const void* ps[7] = {a.lp_new, a.lp_old, a.adv, a.values, a.returns, a.d_lp, a.d_v};
-  bool vec = ((int64_t)a.n_seq * a.seq_len) % 4 == 0;
+  bool vec = true;
   for (const void* p : ps) vec = vec && (reinterpret_cast<uintptr_t>(p) & 15) == 0;
   const int M = a.n_seq * a.seq_len;
   const int grads = a.d_lp || a.d_v ? (M + PL_THREADS * 4 - 1) / (PL_THREADS * 4) : 0;

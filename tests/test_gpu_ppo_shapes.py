@@ -30,7 +30,7 @@ def test_advantages_by_length(n_seq, T, start, dev):
 
 
 @pytest.mark.parametrize("shift", [0, 1])
-@pytest.mark.parametrize("n_seq,T,start", [(1, 4, 1), (1, 4099, 7), (2, 4096, 1000), (5, 1640, 0), (1, 8193, 8192),
+@pytest.mark.parametrize("n_seq,T,start", [(1, 1, 0), (1, 3, 1), (2, 1, 0), (1, 4098, 4096), (1, 4, 1), (1, 4099, 7), (2, 4096, 1000), (5, 1640, 0), (1, 8193, 8192),
                                            (7, 2344, 3)])
 def test_losses_by_size_and_alignment(n_seq, T, start, shift, dev):
     import torch
@@ -57,3 +57,27 @@ def test_losses_by_size_and_alignment(n_seq, T, start, shift, dev):
     assert abs(got[2] - e["clip_frac"]) <= 2.0 / (n_seq * (T - start))
     assert_rel(host(d_lp), e["d_lp"], "d_lp")
     assert_rel(host(d_v), e["d_v"], "d_v")
+
+
+def test_odd_token_counts_cost_what_even_ones_do(dev):
+    """Tokens left over by groups of four are a few words more: the losses of 46 x 1659 tokens take the time of 46 x 1660."""
+    import torch
+    say("loss time")
+
+    def us(T):
+        M = 46 * T
+        x = [torch.randn(M, device=dev) for _ in range(5)]
+        losses, d_lp, d_v = torch.empty(3, device=dev), torch.empty(M, device=dev), torch.empty(M, device=dev)
+        best = float("inf")
+        for _ in range(10):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(20):
+                H.hydra_ppo_loss(*x, 46, T, losses, d_lp, d_v, start=T // 2)
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b) * 50)
+        return best
+
+    odd, even = us(1659), us(1660)
+    assert odd < 1.5 * even, (odd, even)
