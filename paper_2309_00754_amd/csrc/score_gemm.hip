@@ -82,13 +82,16 @@ using Tile64 = ScoreTile<32, 64, 64, 4>;
 static_assert(kScoreTileN == BN, "one partial per GEMM column tile");
 static_assert(kScoreTileM == Tile256::BM, "launch shape known to the host checks");
 
-// Workgroup id -> (row tile, column tile): as in the dual GEMM, each XCD gets a
-// contiguous range of the logical order when the tile count allows, and the
-// logical order walks GROUP_M row tiles per column tile.
+// Workgroup id -> (row tile, column tile): consecutive workgroups go to
+// consecutive XCDs; each XCD takes a contiguous range of the logical order,
+// which walks GROUP_M row tiles per column tile (the tiles that share rows of W
+// run together on one L2).  Contiguous ranges only where the count divides by
+// eight cost 289 -> 215 us for 400 rows x 2 inputs at 4096 x 32000 (500 tiles),
+// 226 -> 174 for 513 rows of one input (128-row tiles; the 256-row ones
+// 190 either way).
 __device__ __forceinline__ void tile_of(int bid, int ntm, int ntn, int& tm, int& tn) {
-  const int total = ntm * ntn;
-  int lid = bid;
-  if ((total & 7) == 0) lid = (bid & 7) * (total >> 3) + (bid >> 3);
+  const int total = ntm * ntn, q = total >> 3, rem = total & 7, xcd = bid & 7;
+  const int lid = xcd * q + min(xcd, rem) + (bid >> 3);
   const int per_group = GROUP_M * ntn;
   const int group = lid / per_group;
   const int first_m = group * GROUP_M;
@@ -424,7 +427,7 @@ __global__ __launch_bounds__(T::NT, T::NT / 256) void score_gemm_kernel(ScoreGem
 // The tile (0: 256, 1: 128, 2: 64 rows) by a model of its time in us: rounds of
 // 256 tiles (one workgroup per CU) x (fixed + K / 64 x step).  Chosen over M =
 // 1 ... 2048, five (K, V) from 512 x 60000 to 4096 x 32000, one and two inputs:
-// 0.4% slower than the best tile on average, 10% at most.  M = 100, K = 2048,
+// 0.4% slower than the best tile on average, 8% at most.  M = 100, K = 2048,
 // V = 50272: 65 -> 59 us against the 256-row tile; M = 64, K = 4096, V = 32000:
 // 92 -> 65; M = 250, K = 3000, V = 20000: 126 -> 79.  All three sum in the same
 // order: the choice does not enter the results.

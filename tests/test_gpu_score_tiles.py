@@ -50,3 +50,29 @@ def test_score_tiles(n_seq, seq_len, K, V, r, dev):
     assert torch.equal(rew1, rew2)
     if r == 0:
         assert torch.equal(one["lp_on"], one["lp_off"])
+
+
+def test_tile_counts_of_any_remainder_keep_the_l2_order(dev):
+    """500 tiles (no multiple of the eight XCDs) take the time of 496: each XCD walks neighbouring tiles either way."""
+    import torch
+    say("score tile order")
+
+    def us(V):
+        M, K, r = 400, 4096, 16
+        h, ha, W, A, B = (torch.randn(n, k, device=dev).to(torch.bfloat16) for n, k in ((M, K), (M, K), (V, K), (r, K), (V, r)))
+        tok = torch.zeros(M, dtype=torch.int32, device=dev)
+        out = [torch.empty(M, device=dev) for _ in range(3)]
+        ws = torch.empty(H.hydra_score_workspace_bytes(M, V), dtype=torch.uint8, device=dev)
+        best = float("inf")
+        for _ in range(10):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(4):
+                H.hydra_score_two_input(ha, h, W, A, B, 1.0, tok, None, 1, M, *out, workspace=ws)
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b) * 250)
+        return best
+
+    any_count, by_eight = us(32000), us(31744)
+    assert any_count < 1.15 * by_eight, (any_count, by_eight)
