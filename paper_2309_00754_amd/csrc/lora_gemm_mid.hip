@@ -31,11 +31,10 @@
 namespace hydra {
 namespace {
 
-// Up to kFewRows rows only tiles of at most kFewTileMax outputs serve, and the
-// sums run in short chains: a decode step's outputs keep the error that sums
-// spread over many waves give.
+// Up to kFewRows rows tiles of kFewRows rows serve, and the sums run in short
+// chains: a decode step's outputs keep the error that sums spread over many
+// waves give.
 constexpr int kFewRows = 16;
-constexpr int kFewTileMax = 64 * 64;
 constexpr int kFoldSlabs = 4;
 
 struct MidArgs {
@@ -66,11 +65,14 @@ constexpr size_t cmax(size_t a, size_t b) { return a > b ? a : b; }
 
 // TM x TN output tile, WM x WN sub-tile per wave, KS waves per sub-tile, BK
 // wide K slabs in a ring of NS stages, RA rows of A in every slab (the padded
-// rank, 0: none).
-template <int TM_, int TN_, int WM_, int WN_, int KS_, int BK_, int NS_, int RA_>
+// rank, 0: none).  A tile of 16 rows or columns lies in a sub-tile of 32 whose
+// second half repeats the first and is not written.
+template <int TM_, int TN_, int WM_, int WN_, int KS_, int BK_, int NS_, int WPC_, int RA_>
 struct GemmMid {
   static constexpr int TM = TM_, TN = TN_, WM = WM_, WN = WN_, KS = KS_, BK = BK_, RA = RA_;
-  static constexpr int NWM = TM / WM, NWN = TN / WN, NW = NWM * NWN * KS, NT = NW * 64;
+  static constexpr int NWM = TM < WM ? 1 : TM / WM, NWN = TN < WN ? 1 : TN / WN, NW = NWM * NWN * KS, NT = NW * 64;
+  static constexpr int XMASK = TM < 32 ? TM - 1 : -1, WMASK = TN < 32 ? TN - 1 : -1;  // row of a tile from that of a sub-tile
+  static constexpr int TROWS = TM < WM ? TM : WM;  // rows of T of a row block
   static constexpr int MT = WM / 32, NTL = WN / 32, NQ = MT * NTL;
   static constexpr int CPR = BK / 8;               // 16-byte chunks per LDS row
   static constexpr int RPB = 64 / CPR;             // rows per copy instruction
@@ -83,16 +85,21 @@ struct GemmMid {
   static constexpr int HS = SPW >= 2 ? SPW / 2 : 1;         // 32-wide k-steps of T per wave and slab
   static constexpr int TSPLIT = SPW >= 2 ? 1 : 2;           // waves that share one of them
   static constexpr int TKS = KS / TSPLIT;                   // partial sums of T
-  static constexpr int TPW = RA > 0 ? WM / 16 / NWN / TSPLIT : 1;  // 16-row T tiles per wave
-  static constexpr int EXB = KS > 1 ? NW * NQ * 2 * 1024 : 0;      // exchange buffer of the reduce-scatter
-  static constexpr int TRB = RA > 0 ? TKS * TM * RA * 4 : 0;       // partial T
+  static constexpr int TPW = RA > 0 ? TROWS / 16 / NWN / TSPLIT : 1;  // 16-row T tiles per wave
+  // The partial sums of the KS waves meet in steps (reduce-scatter), or, on the
+  // 16-row tiles, all at once: there the epilogue is a fifth of a small call, and
+  // the fewer barriers take 0.25 us off it.
+  static constexpr bool AT_ONCE = TM < 32;
+  static constexpr int EXB = KS > 1 ? NW * NQ * (AT_ONCE ? 4 : 2) * 1024 : 0;  // exchange buffer
+  static constexpr int TRB = RA > 0 ? TKS * TM * RA * 4 : 0;                   // partial T
+  static constexpr size_t RED = AT_ONCE ? EXB + TRB : cmax(EXB, TRB);
   // s T as bf16 parts, each the rounding error of the ones before: three of
   // them hold all 24 bits (error of y_on against 64 bits 4e-7, with two 2.2e-6)
   static constexpr int BSB = TN * RA * 2;                          // bytes of B's LDS copy
-  static constexpr int NP = BSB + TM * 3 * RA * 2 + cmax(EXB, TRB) <= 160 * 1024 ? 3 : 2;
+  static constexpr int NP = BSB + TM * 3 * RA * 2 + RED <= 160 * 1024 ? 3 : 2;
   static constexpr int TSB = TM * NP * RA * 2;                     // ... and of s T's
-  static constexpr size_t EPI = BSB + TSB + cmax(EXB, TRB);
-  static constexpr size_t kLds = 160 * 1024;
+  static constexpr size_t EPI = BSB + TSB + RED;
+  static constexpr size_t kLds = 160 * 1024 / WPC_;
   // fewer stages where they do not fit with the rows of A; an even number where
   // a slab is one k-step (its two fragment sets then alternate with the stages)
   static constexpr int FIT = int((kLds / 16 - PAD) / STAGE);
@@ -102,8 +109,10 @@ struct GemmMid {
   static_assert(NS >= 2 && (SPW == 1 || SPW % 2 == 0), "ring and k-steps");
   static_assert(LDS <= kLds, "fits in LDS");
   static_assert(NU % KS == 0, "the reduce-scatter ends with whole units");
-  static_assert(RA == 0 || TM * TN > kFewTileMax || NP == 3, "every bit of s T on the tiles that serve few rows");
-  static_assert(RA == 0 || TPW * NWN * TSPLIT * 16 == WM, "T rows split over the waves of a row block");
+  static_assert(!AT_ONCE || (KS == 4 && NWM * NWN == 1), "four partial sums of one sub-tile");
+  static_assert(RA == 0 || TM > kFewRows || NP == 3, "every bit of s T on the tiles that serve few rows");
+  static_assert(RA == 0 || TPW * NWN * TSPLIT * 16 == TROWS, "T rows split over the waves of a row block");
+  static_assert((TM >= 32 || TM == 16) && (TN >= 32 || TN == 16), "whole 16-row fragments of T, whole units of a block");
 };
 
 template <int V>
@@ -235,9 +244,9 @@ __global__ __launch_bounds__(G::NT, G::NT / 256) void lora_gemm_mid_kernel(MidAr
     const uint4* s = sm + stage * STAGE;
     const int ch = 2 * (kg * SPW + st) + lh;
     if (q < NTL)
-      f.w[q] = s[lds_idx(WROW + wc * WN + q * 32 + l32, ch)];
+      f.w[q] = s[lds_idx(WROW + wc * WN + ((q * 32 + l32) & G::WMASK), ch)];
     else
-      f.x[q - NTL] = s[lds_idx(XROW + wr * WM + (q - NTL) * 32 + l32, ch)];
+      f.x[q - NTL] = s[lds_idx(XROW + wr * WM + (((q - NTL) * 32 + l32) & G::XMASK), ch)];
   };
   auto read_t = [&](int stage, int r) __attribute__((always_inline)) {
     const uint4* s = sm + stage * STAGE;
@@ -420,12 +429,40 @@ __global__ __launch_bounds__(G::NT, G::NT / 256) void lora_gemm_mid_kernel(MidAr
       stage_update();
     }
   }
+  // The KS partial sub-tiles, in units of four registers (unit u = 4 (mi NTL + ni)
+  // + i), are summed over the waves in the order (0 + 1) + (2 + 3); afterwards
+  // this wave holds the NU / KS units from u0.
+  int u0 = 0;
+  f32x4_t un[NU];
+#pragma unroll
+  for (int q = 0; q < NQ; ++q)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      un[q * 4 + i] = f32x4_t{acc[q / NTL][q % NTL][4 * i], acc[q / NTL][q % NTL][4 * i + 1],
+                              acc[q / NTL][q % NTL][4 * i + 2], acc[q / NTL][q % NTL][4 * i + 3]};
+  f32x4_t* const ex = reinterpret_cast<f32x4_t*>(scratch);
+  if constexpr (G::AT_ONCE) {
+#pragma unroll
+    for (int u = 0; u < NU; ++u) ex[(u * KS + kg) * 64 + lane] = un[u];
+  }
+  auto sum_at_once = [&]() __attribute__((always_inline)) {
+    u0 = kg * (NU / KS);
+#pragma unroll
+    for (int u = 0; u < NU / KS; ++u) {
+      const f32x4_t* p = ex + (u0 + u) * KS * 64 + lane;
+      un[u] = (p[0] + p[64]) + (p[128] + p[192]);
+    }
+  };
+  if constexpr (G::AT_ONCE && RA == 0) {
+    __syncthreads();
+    sum_at_once();
+  }
   if constexpr (RA > 0) {
 #pragma unroll
     for (int i = 0; i < BPT; ++i)
       if (t + i * NT < TN * RA) Bs[t + i * NT] = (uint16_t)bv[i];
     // accT[q][j] holds T[trow + 16 q + 4 lg + e][16 j + l16] over this wave's k values
-    float* tp = reinterpret_cast<float*>(scratch);
+    float* tp = reinterpret_cast<float*>(scratch + (G::AT_ONCE ? G::EXB : 0));
 #pragma unroll
     for (int q = 0; q < TPW; ++q)
 #pragma unroll
@@ -434,6 +471,7 @@ __global__ __launch_bounds__(G::NT, G::NT / 256) void lora_gemm_mid_kernel(MidAr
         for (int e = 0; e < 4; ++e)
           tp[((kg / G::TSPLIT) * TM + trow + q * 16 + 4 * lg + e) * RA + 16 * j + l16] = accT[q][j][e];
     __syncthreads();
+    if constexpr (G::AT_ONCE) sum_at_once();
     for (int e = t; e < TM * RA; e += NT) {
       float v = tp[e];
 #pragma unroll
@@ -450,20 +488,9 @@ __global__ __launch_bounds__(G::NT, G::NT / 256) void lora_gemm_mid_kernel(MidAr
     __syncthreads();
   }
 
-  // Reduce-scatter of the KS partial sub-tiles over units of four registers
-  // (unit u = 4 (mi NTL + ni) + i): at step 2^b the waves kg and kg ^ 2^b
-  // exchange halves of the units they still hold.  Afterwards this wave holds
-  // the NU / KS units from u0.
-  f32x4_t un[NU];
-#pragma unroll
-  for (int q = 0; q < NQ; ++q)
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      un[q * 4 + i] = f32x4_t{acc[q / NTL][q % NTL][4 * i], acc[q / NTL][q % NTL][4 * i + 1],
-                              acc[q / NTL][q % NTL][4 * i + 2], acc[q / NTL][q % NTL][4 * i + 3]};
-  int u0 = 0;
-  if constexpr (KS > 1) {
-    f32x4_t* ex = reinterpret_cast<f32x4_t*>(scratch);
+  // Reduce-scatter: at step 2^b the waves kg and kg ^ 2^b exchange halves of the
+  // units they still hold.
+  if constexpr (!G::AT_ONCE && KS > 1) {
     constexpr int HALF = NU / 2;
     auto step = [&](auto BIT, auto CNT) __attribute__((always_inline)) {
       constexpr int bit = decltype(BIT)::value, cnt = decltype(CNT)::value;
@@ -502,11 +529,12 @@ __global__ __launch_bounds__(G::NT, G::NT / 256) void lora_gemm_mid_kernel(MidAr
     const int row = m0 + wr * WM + mi * 32 + l32;
     const int colb = n0 + wc * WN + ni * 32 + 4 * lh;
     auto store = [&](float* y, const f32x4_t (&v)[UPQ]) __attribute__((always_inline)) {
-      if (row >= M) return;
+      if (row >= M || (TM < 32 && l32 >= TM)) return;
       float* yr = y + (size_t)row * N;
 #pragma unroll
       for (int k = 0; k < UPQ; ++k) {
         const int col = colb + 8 * (i0 + k);
+        if (TN < 32 && col >= n0 + TN) continue;
         if (g.vec4 && col + 3 < N) {
           *reinterpret_cast<f32x4_t*>(yr + col) = v[k];
         } else {
@@ -547,8 +575,10 @@ __global__ __launch_bounds__(G::NT, G::NT / 256) void lora_gemm_mid_kernel(MidAr
 #pragma unroll
         for (int ks = 0; ks < NP * RA / 16; ++ks) {
           const int k = ks * 16 + lh * 8;
-          const uint4 bf = *reinterpret_cast<const uint4*>(Bs + (wc * WN + ni * 32 + l32) * RA + k % RA1);
-          const uint4 tf = *reinterpret_cast<const uint4*>(Ts + (wr * WM + mi * 32 + l32) * NP * RA + k);
+          const uint4 bf =
+              *reinterpret_cast<const uint4*>(Bs + (wc * WN + ((ni * 32 + l32) & G::WMASK)) * RA + k % RA1);
+          const uint4 tf =
+              *reinterpret_cast<const uint4*>(Ts + (wr * WM + ((mi * 32 + l32) & G::XMASK)) * NP * RA + k);
           L = mfma32(bf, tf, L);
         }
       }
@@ -587,10 +617,7 @@ __global__ __launch_bounds__(G::NT, G::NT / 256) void lora_gemm_mid_kernel(MidAr
 // long as it still gives 256 tiles.
 // M x K x N, us: 48 x 4096 x 4096 41.4 -> 11.6, 333 x 4096 x 11008 72 -> 58,
 // 512 x 4096 x 4096 47.6 -> 29.9, 1000 x 11008 x 4096 157 -> 121, 500 x 2048 x
-// 2048 30.2 -> 13.6 (128 x 256 tile -> here, rank 16).  Rows 9 to 16, against
-// a kernel whose 16 waves split K over 16 to 64 columns: four 4096 x 4096 40.2
-// -> 38.4 at rank 16, 52.9 -> 51.2 at rank 64; four 2048 x 2048 14.5 -> 10.8
-// and 23.0 -> 15.0; one 512 x 512 7.7 -> 6.2.
+// 2048 30.2 -> 13.6 (128 x 256 tile -> here, rank 16).
 struct MidTile {
   int tm, tn;
   float base, fixed, step;
@@ -627,25 +654,38 @@ void launch_tile(MidArgs& g, hipStream_t stream) {
 
 template <class G>
 void launch_plain(MidArgs& g, hipStream_t stream) {
-  if constexpr (G::TM * G::TN <= kFewTileMax)
-    if (g.ga.M <= kFewRows && g.ga.K > kFoldSlabs * G::BK) return launch_tile<G, PLAIN, true>(g, stream);
+  if constexpr (G::TM == kFewRows)
+    if (g.ga.K > kFoldSlabs * G::BK) return launch_tile<G, PLAIN, true>(g, stream);
   launch_tile<G, PLAIN>(g, stream);
+}
+
+// Workgroups per CU that the ring leaves room for: two on the 16-row tiles
+// wherever half of the LDS holds three slabs (a ring of 8 and one workgroup
+// otherwise: with two slabs a long K waits for every copy).
+constexpr int per_cu(int tm, int tn, int ra) {
+  return tm == kFewRows && tn > 16 && 80 * 1024 / ((tm + tn + ra) * 256) >= 3 ? 2 : 1;
 }
 
 template <int TM, int TN, int WM, int WN, int KS, int BK, int NS>
 hipError_t launch_mid(MidArgs& g, int ra, hipStream_t stream) {
-  if (g.nkc[0] > 0)
-    launch_tile<GemmMid<TM, TN, WM, WN, KS, BK, NS, 0>, PART>(g, stream);
-  else if (g.rp > 0)
-    launch_tile<GemmMid<TM, TN, WM, WN, KS, BK, NS, 0>, PRE>(g, stream);
-  else if (ra == 0)
-    launch_plain<GemmMid<TM, TN, WM, WN, KS, BK, NS, 0>>(g, stream);
+  if constexpr (TM != kFewRows) {
+    if (g.nkc[0] > 0) {
+      launch_tile<GemmMid<TM, TN, WM, WN, KS, BK, NS, 1, 0>, PART>(g, stream);
+      return hipGetLastError();
+    }
+    if (g.rp > 0) {
+      launch_tile<GemmMid<TM, TN, WM, WN, KS, BK, NS, 1, 0>, PRE>(g, stream);
+      return hipGetLastError();
+    }
+  }
+  if (ra == 0)
+    launch_plain<GemmMid<TM, TN, WM, WN, KS, BK, NS, per_cu(TM, TN, 0), 0>>(g, stream);
   else if (ra == 16)
-    launch_plain<GemmMid<TM, TN, WM, WN, KS, BK, NS, 16>>(g, stream);
+    launch_plain<GemmMid<TM, TN, WM, WN, KS, BK, NS, per_cu(TM, TN, 16), 16>>(g, stream);
   else if (ra == 32)
-    launch_plain<GemmMid<TM, TN, WM, WN, KS, BK, NS, 32>>(g, stream);
+    launch_plain<GemmMid<TM, TN, WM, WN, KS, BK, NS, per_cu(TM, TN, 32), 32>>(g, stream);
   else if (ra == 64)
-    launch_plain<GemmMid<TM, TN, WM, WN, KS, BK, NS, 64>>(g, stream);
+    launch_plain<GemmMid<TM, TN, WM, WN, KS, BK, NS, per_cu(TM, TN, 64), 64>>(g, stream);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();
@@ -663,16 +703,65 @@ hipError_t launch_any(MidArgs& g, int ra, int tile, hipStream_t stream) {
   }
 }
 
+// Up to 16 rows without the pre-pass: 16 x 16, 16 x 32 and 16 x 64 tiles.  All
+// three sum in the same order (KS, BK and the folds are theirs in common), so
+// that this choice, unlike gemm_mid_tile's, may look at the rank and at the
+// members of the launch and an output still has the same bits in every call.
+// Model as kMidTiles', slabs of 128 k values: with two workgroups per CU a pair
+// takes `pair` per slab.  Fits over 9 and 16 rows, 1 to 8 members, 17 (K, N) from
+// 512 x 512 to 4096 x 32000 (rms error 6-20%; the choice is 3% slower than the
+// best of six forms on average, and at most 5% slower than the 32-row tiles).
+// What they say: few workgroups wait for each slab's latency, so narrow tiles and
+// a deep ring win; many are bound by the copies of x and A's rows, which a wider
+// tile shares among more outputs.
+// us, 9 rows, the 16-wave kernel that split K over 16 to 64 columns -> 32-row
+// tiles chosen without rank and members -> here: 4096 x 4096 rank 8 11.7 -> 14.2
+// -> 10.6; 8192 x 2048 rank 0 14.6 -> 17.9 -> 12.0; 4096 x 1024 rank 8 11.3 ->
+// 14.2 -> 9.7; four 2048 x 8192 rank 64 54 -> 68 -> 39; eight 1000 x 3000 rank 32
+// 20 -> 24 -> 19.  Left slower than that first kernel, by 2 to 8%: 520 x 1000 and
+// smaller.
+struct FewCost {
+  float base, fixed, step, pair;
+};
+constexpr FewCost kFewCosts[3][4] = {
+    // rank 0, 16, 32, 64
+    {{2.40f, 0.83f, 0.162f, 0.f}, {1.51f, 2.66f, 0.186f, 0.f}, {1.23f, 3.54f, 0.263f, 0.f}, {1.08f, 4.85f, 0.389f, 0.f}},
+    {{1.78f, 1.64f, 0.238f, 0.689f}, {1.24f, 2.98f, 0.279f, 0.715f}, {1.13f, 3.34f, 0.268f, 0.818f}, {0.26f, 5.56f, 0.488f, 0.f}},
+    {{0.56f, 2.91f, 0.314f, 1.327f}, {0.f, 4.39f, 0.415f, 1.386f}, {0.f, 5.28f, 0.521f, 0.f}, {0.f, 6.07f, 0.566f, 0.f}}};
+
+hipError_t launch_few(MidArgs& g, int ra, hipStream_t stream) {
+  int best = 0;
+  float cost = 0.f;
+  for (int i = 0; i < 3; ++i) {
+    const int tn = 16 << i;
+    const FewCost& c = kFewCosts[i][ra == 0 ? 0 : ra == 16 ? 1 : ra == 32 ? 2 : 3];
+    const int per = ((g.ga.N + tn - 1) / tn * g.ga.G + 255) / 256;  // workgroups for every CU
+    const float slabs = (float)((g.ga.K + 127) / 128);
+    const int pairs = c.pair > 0.f ? per / 2 : 0, ones = per - 2 * pairs;
+    const float t = c.base + (float)pairs * (c.fixed + slabs * c.pair) + (float)ones * (c.fixed + slabs * c.step);
+    if (i == 0 || t < cost) {
+      cost = t;
+      best = i;
+    }
+  }
+  switch (best) {
+    case 0: return launch_mid<16, 16, 32, 32, 4, 128, 8>(g, ra, stream);
+    case 1: return launch_mid<16, 32, 32, 32, 4, 128, 8>(g, ra, stream);
+    default: return launch_mid<16, 64, 32, 64, 4, 128, 8>(g, ra, stream);
+  }
+}
+
 }  // namespace
 
 int gemm_mid_tile(int M, int N, int K) {
-  // Up to 16 rows always one of the tiles up to 64 x 64: they carry s T in all
-  // its 24 bits (128 x 192 holds two bf16 parts of it) and sum in short chains.
+  // Up to 16 rows always a small tile: launch_few's, which carry s T in all its
+  // 24 bits and sum in short chains, or with the pre-pass (the backward's dx) one
+  // of the two of 32 rows.
   const bool few = M <= kFewRows;
   int best = few ? 0 : -1;
   float cost = tile_cost(few ? kMidTiles[0] : kBigTile, M, N, K);
   for (int i = 0; i < kMidTileCount; ++i) {
-    if (few && kMidTiles[i].tm * kMidTiles[i].tn > kFewTileMax) break;
+    if (few && i > 1) break;
     const float c = tile_cost(kMidTiles[i], M, N, K);
     if (c < cost) {
       cost = c;
@@ -696,7 +785,8 @@ hipError_t launch_lora_gemm_mid(const GroupArgs& ga, const uint16_t* const* ts, 
              (reinterpret_cast<uintptr_t>(ga.y_on[i]) & 15) == 0;
     any_on = any_on || (ga.y_on[i] && ga.A[i] && ga.B[i]);
   }
-  return launch_any(g, any_on ? padded_rank(ga.r) : 0, tile, stream);
+  const int ra = any_on ? padded_rank(ga.r) : 0;
+  return ga.M <= kFewRows && rp_pre == 0 ? launch_few(g, ra, stream) : launch_any(g, ra, tile, stream);
 }
 
 hipError_t launch_t_part_mid(const TpreArgs* as, int n, int rp, int* nkc, hipStream_t stream) {

@@ -119,6 +119,55 @@ def test_few_rows_keep_the_bits_of_t(M, N, K, r, dev):
     assert torch.equal(y_off, alone)
 
 
+@pytest.mark.parametrize("G,M,N,K,r", [(8, 9, 3000, 1000, 64), (4, 16, 8200, 264, 16), (3, 12, 4096, 520, 32), (8, 10, 700, 72, 8),
+                                       (2, 16, 5001, 1032, 0), (8, 9, 2048, 2048, 0)])
+def test_few_rows_have_the_same_bits_on_every_tile(G, M, N, K, r, dev):
+    """Up to 16 rows the tile depends on the rank and on the members of a launch; an output does not."""
+    import torch
+    say("few rows, group", G, M, N, K, r)
+    ms = [WL.gen_linear(9500 + i + N + K + r, M, K, N, r) for i in range(G)]
+    xs, Ws = [dev_bf16(c.x, dev) for c in ms], [dev_bf16(c.W, dev) for c in ms]
+    As, Bs = ([dev_bf16(c.A, dev) for c in ms], [dev_bf16(c.B, dev) for c in ms]) if r else ([None] * G, [None] * G)
+    ss = [c.s + i for i, c in enumerate(ms)]
+    offs, ons = [_nan(M, N, dev) for _ in range(G)], [_nan(M, N, dev) for _ in range(G)]
+    H.hydra_lora_linear_group(xs, Ws, As, Bs, ss, offs, ons)
+    for i, c in enumerate(ms):
+        off, on, alone = _nan(M, N, dev), _nan(M, N, dev), _nan(M, N, dev)
+        H.hydra_lora_linear(xs[i], Ws[i], As[i], Bs[i], ss[i], off, on)
+        H.hydra_lora_linear(xs[i], Ws[i], None, None, 0.0, alone, None)
+        torch.cuda.synchronize()
+        assert torch.equal(offs[i], off) and torch.equal(ons[i], on) and torch.equal(alone, off), i
+        e_off, e_on = lora_linear_ref(c.x, c.W, c.A, c.B, ss[i])
+        assert_rel(host(off), e_off, "y_off")
+        assert_rel(host(on), e_on, "y_on")
+
+
+def test_few_rows_cost_less_than_a_wider_tile(dev):
+    """Nine rows of 8192 x 2048 take clearly less than seventeen, whose tile copies twice the rows (on one tile with them
+    they took the same, 18 us, where the kernel for few rows before it took 15)."""
+    import torch
+    say("few rows time")
+    K, N, n = 8192, 2048, 12
+    Ws = [torch.randn(N, K, device=dev).to(torch.bfloat16) for _ in range(n)]  # more than the caches hold
+
+    def us(M):
+        x, off = torch.randn(M, K, device=dev).to(torch.bfloat16), torch.empty(M, N, device=dev)
+        best = float("inf")
+        for _ in range(20):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for W in Ws * 4:
+                H.hydra_lora_linear(x, W, None, None, 0.0, off, None)
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b) * 1e3 / (4 * n))
+        return best
+
+    few, more = us(9), us(17)
+    say(f"{few:.2f} {more:.2f} us")
+    assert few < 0.9 * more, (few, more)
+
+
 def test_an_infinite_t_gives_infinite_outputs(dev):
     import torch
     say("infinite t")
