@@ -215,15 +215,25 @@ __global__ __launch_bounds__(S_WAVES * 64) void lora_t_small_kernel(TpreJobs job
 }
 
 // Where the one launch is faster than partial sums + finish (and the gap of
-// about 1.5 us between them), us at M = 1024: rank 16, K = 2048 7.0 against 4.6
-// + 4.1, K = 4096 9.7 against 4.8 + 5.0, K = 8192 16.7 against 6.0 + 4.9; rank
-// 128, K = 2048 9.9 against 5.8 + 4.8.  Only while its workgroups are at most
-// 256, one round (M = 2048, rank 128: 18.1 against 7 + 5; the backward's two
-// jobs at M = 2510, K = 4096, rank 16: 16.9 against 11.4 + 4.8).
+// about 1.5 us between them): K short enough that one workgroup's walk over it
+// takes no longer than the two launches, or (up to K = 4096 at ranks 16 and 32,
+// in the backward up to 2048 at 64 and 128) so many rows that the partial sums
+// fill the chip more than once.  Only while its workgroups are
+// at most 256, one round (M = 2048, rank 128: 18.1 against 7 + 5; the backward's
+// two jobs at M = 2510, K = 4096, rank 16: 16.9 against 11.4 + 4.8).  us a whole
+// call, one launch against two, by (rank, K, workgroups): scoring (16, 1000, 64)
+// -1.8, (32, 1000, 64) -1.1, (64, 1000, 64) -2.1, (128, 1000, 64) -2.3; linears and
+// backward (16, 3000, 64) -0.1, (16, 4096, 64) +2.0, (16, 4096, 128) 0, (16, 4096,
+// 176) -1.2, (16, 4096, 256) -3 to -5, (32, 2048, 64) +1.0, (32, 2048, 176) -1.5,
+// (32, 4096, 64) +4.5, (32, 4096, 256) -4, (64, 2048, 84) +0.4, (64, 2048,
+// 256) in the backward -1.3, (128, 2048, 84) +0.4; members of a group count one by one, for the bits of T, and take +3 to
+// +13 where they are more than 256 together.
 bool use_small(const TpreArgs& a, int rp) {
   const int K = a.Kform > 0 ? a.Kform : a.K;
   const int64_t groups = (int64_t)((a.M + 15) / 16) * (rp / 16 / small_jt(rp)) * (a.Kall > 0 ? 2 : 1);
-  return K <= (rp <= 32 ? 4096 : 2048) && groups <= 256;
+  if (groups > 256) return false;
+  const int kmany = rp <= 32 ? 4096 : a.Kall > 0 ? 2048 : 0;
+  return K <= (rp == 16 ? 3072 : 1024) || (K <= kmany && groups >= 160);
 }
 
 // Workgroups [bbeg[j], bbeg[j + 1]) finish job j; those past the last job's

@@ -4,9 +4,10 @@
 import numpy as np
 import pytest
 
+import paper_2309_00754_amd as H
 import workloads as WL
-from oracle import lora_linear_backward_ref
-from gpu_helpers import assert_rel, say
+from oracle import lora_linear_backward_ref, score_head_ref
+from gpu_helpers import assert_abs, assert_rel, dev_bf16, host, say
 from test_gpu_backward import _run
 
 pytestmark = pytest.mark.gpu
@@ -28,3 +29,28 @@ def test_backward_plans(M, K, N, r, dev):
         assert_rel(got, want, name)
     for i, name in enumerate(("dx", "dA", "dB")):
         assert np.array_equal(_run(case, dev, want=(name,))[i], full[i]), name
+
+
+def _touched(ws):
+    """Whether any byte of a workspace filled with 0xAB was written."""
+    return bool((ws != 0xAB).any().item())
+
+
+@pytest.mark.parametrize("M,K,r,one", [(64, 1024, 32, True), (64, 1032, 32, False), (64, 4096, 16, False), (64, 3072, 16, True),
+                                       (2560, 4096, 16, True), (2559, 4096, 32, True), (4100, 264, 16, False),
+                                       (64, 1024, 128, True), (1024, 2048, 128, False)])
+def test_one_launch_where_k_is_short_or_rows_many(M, K, r, one, dev):
+    """The pre-pass of the scoring pass leaves partial sums in the end of the workspace only where it takes two launches."""
+    import torch
+    say("pre-pass plan", M, K, r)
+    V = 40
+    s = WL.gen_score_head(1400 + M + K + r, 1, M, K, V, r)
+    ws = torch.full((H.hydra_score_workspace_bytes(M, V),), 0xAB, dtype=torch.uint8, device=dev)
+    out = [torch.full((M,), float("nan"), device=dev) for _ in range(3)]
+    H.hydra_score(dev_bf16(s.h, dev), dev_bf16(s.W_lm, dev), dev_bf16(s.A, dev), dev_bf16(s.B, dev), s.s,
+                  torch.from_numpy(s.ids).to(dev), None, 1, M, *out, workspace=ws)
+    torch.cuda.synchronize()
+    assert _touched(ws[-8 * M * 128 * 4:]) == (not one)
+    e = score_head_ref(s.h, s.W_lm, s.A, s.B, s.s, s.ids, s.w_rm, 1, M)
+    for got, k in zip(out, ("lp_on", "lp_off", "kl")):
+        assert_abs(host(got), e[k], k)
