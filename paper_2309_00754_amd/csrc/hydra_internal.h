@@ -228,6 +228,9 @@ constexpr int kGemmThreads = 512;
 // inputs, or -1 where the 128 x 256 tile is the better one.  It depends on
 // these sizes alone: every entry point sums an output in the same order.
 int gemm_mid_tile(int M, int N, int K);
+// Whether T formed in these tiles (padded rank up to 64) costs less than the
+// pre-pass, which needs a workspace; false where gemm_mid_tile gives none.
+bool gemm_mid_in_tile(int M, int N, int K, int rp);
 // The members of ga on that tile, in one launch.  With ts / bp the
 // LoRA update comes from the pre-pass (rp_pre the padded rank, ts[i] null: no
 // adapter); without, from A and B (padded rank up to 64).

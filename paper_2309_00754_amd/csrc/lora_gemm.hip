@@ -581,10 +581,7 @@ hipError_t launch_lora_gemm(const LinearArgs& a, hipStream_t stream) {
 
 hipError_t launch_lora_gemm_tpre(const LinearArgs& a, uint16_t* ts, uint16_t* bp, float* part, hipStream_t stream) {
   const int rp = a.y_on ? padded_rank(a.r) : 0;
-  // On the smaller tiles T in the tile (up to padded rank 64) costs less than
-  // the pre-pass's two launches (10-14 us): 333 x 2048 x 2000 at rank 64 takes
-  // 16.6 us in one launch against 11.7 + 12.
-  if (rp <= 64 && (rp == 0 || gemm_mid_tile(a.M, a.N, a.K) >= 0)) return launch_lora_gemm(a, stream);
+  if (rp == 0 || gemm_mid_in_tile(a.M, a.N, a.K, rp)) return launch_lora_gemm(a, stream);
   TpreArgs t{};
   t.x = a.x;
   t.A = a.A;

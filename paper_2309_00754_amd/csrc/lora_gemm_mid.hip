@@ -610,9 +610,8 @@ __global__ __launch_bounds__(G::NT, G::NT / 256) void lora_gemm_mid_kernel(MidAr
 // of 256 tiles (one workgroup per CU) and slabs of 64 k values.  The numbers
 // are fits to kernel times over M = 17 ... 4096 and eight (K, N) from 700 to
 // 11008 at rank 16 (rms error 11-18%; the model's choice is 0.4% slower than
-// the best one on average, 16% at most, and never slower than the 128 x 256
-// tile by more than 1.2% there; 1100 x 4096 x 4096 and 2100 x 2048 x 8192 are,
-// by 4% and 2%).  What they say: a 64-wide slab of a tile costs its bytes at 66
+// the best one on average, 16% at most).
+// What they say: a 64-wide slab of a tile costs its bytes at 66
 // to 74 GB/s per CU whatever the tile, so a larger one is cheaper per output as
 // long as it still gives 256 tiles.
 // M x K x N, us: 48 x 4096 x 4096 41.4 -> 11.6, 333 x 4096 x 11008 72 -> 58,
@@ -769,6 +768,20 @@ int gemm_mid_tile(int M, int N, int K) {
     }
   }
   return best;
+}
+
+// On the smaller tiles T in the tile costs less than the pre-pass's launches
+// (10-14 us): 333 x 2048 x 2000 at rank 64 takes 16.6 us in one launch against
+// 11.7 + 12.  Not where 128 x 192 tiles of padded rank 64 run more than one
+// round: A adds a fifth to every slab of each round, and the pre-pass pays once
+// (in the tile -> pre-pass, us: 2692 x 4096 x 4096 132 -> 122, 2300 x 11008 x 4096
+// 300 -> 266, 2796 x 3000 x 6000 224 -> 203; 0.94 on average, 1.04 at most).
+bool gemm_mid_in_tile(int M, int N, int K, int rp) {
+  const int tile = gemm_mid_tile(M, N, K);
+  if (tile < 0 || rp > 64) return false;
+  const MidTile& c = kMidTiles[tile];
+  const int64_t tiles = (int64_t)((M + c.tm - 1) / c.tm) * ((N + c.tn - 1) / c.tn);
+  return !(rp == 64 && tile == kMidTileCount - 1 && tiles > 256);
 }
 
 hipError_t launch_lora_gemm_mid(const GroupArgs& ga, const uint16_t* const* ts, const uint16_t* const* bp, int rp_pre,

@@ -6,7 +6,7 @@ import pytest
 
 import paper_2309_00754_amd as H
 import workloads as WL
-from oracle import lora_linear_backward_ref, score_head_ref
+from oracle import lora_linear_backward_ref, lora_linear_ref, score_head_ref
 from gpu_helpers import assert_abs, assert_rel, dev_bf16, host, say
 from test_gpu_backward import _run
 
@@ -34,6 +34,26 @@ def test_backward_plans(M, K, N, r, dev):
 def _touched(ws):
     """Whether any byte of a workspace filled with 0xAB was written."""
     return bool((ws != 0xAB).any().item())
+
+
+@pytest.mark.parametrize("M,N,K,r,pre", [(1030, 8200, 264, 64, True), (1030, 8200, 264, 33, True), (1030, 8200, 264, 32, False),
+                                         (384, 12288, 256, 64, False)])
+def test_rank_64_takes_the_pre_pass_where_its_tiles_run_several_rounds(M, N, K, r, pre, dev):
+    """387 and 192 tiles of 128 x 192; the workspace shows which way the update went.  y_off has the plain call's bits."""
+    import torch
+    say("rank 64 route", M, N, K, r)
+    c = WL.gen_linear(1300 + M + N + r, M, K, N, r)
+    x, W, A, B = (dev_bf16(v, dev) for v in (c.x, c.W, c.A, c.B))
+    ws = torch.full((H.hydra_lora_linear_workspace_bytes(M, N, r),), 0xAB, dtype=torch.uint8, device=dev)
+    off, on, plain = (torch.full((M, N), float("nan"), device=dev) for _ in range(3))
+    H.hydra_lora_linear_ws(x, W, A, B, c.s, off, on, ws)
+    H.hydra_lora_linear(x, W, A, B, c.s, plain, None)
+    torch.cuda.synchronize()
+    assert _touched(ws) == pre
+    assert torch.equal(off, plain)
+    e_off, e_on = lora_linear_ref(c.x, c.W, c.A, c.B, c.s)
+    assert_rel(host(off), e_off, "y_off")
+    assert_rel(host(on), e_on, "y_on")
 
 
 @pytest.mark.parametrize("M,K,r,one", [(64, 1024, 32, True), (64, 1032, 32, False), (64, 4096, 16, False), (64, 3072, 16, True),
