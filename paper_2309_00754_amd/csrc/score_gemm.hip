@@ -322,15 +322,14 @@ __global__ __launch_bounds__(T::NT, T::NT / 256) void score_gemm_kernel(ScoreGem
       float mx = -INFINITY;
 #pragma unroll
       for (int q = 0; q < 32; ++q) mx = fmaxf(mx, z[b * 32 + q]);
+      // e^(z - mx) = 2^(z log2 e - mx log2 e); without a maximum (no column of the
+      // vocabulary, or only NaN, which a maximum passes over) e^z: 0, or NaN
       float s0 = 0.f, s1 = 0.f;
-      if (mx != -INFINITY) {
-        // e^(z - mx) = 2^(z log2 e - mx log2 e)
-        const float mxs = mx * kLog2e;
+      const float mxs = mx == -INFINITY ? 0.f : mx * kLog2e;
 #pragma unroll
-        for (int q = 0; q < 32; q += 2) {
-          s0 += __builtin_amdgcn_exp2f(fmaf(z[b * 32 + q], kLog2e, -mxs));
-          s1 += __builtin_amdgcn_exp2f(fmaf(z[b * 32 + q + 1], kLog2e, -mxs));
-        }
+      for (int q = 0; q < 32; q += 2) {
+        s0 += __builtin_amdgcn_exp2f(fmaf(z[b * 32 + q], kLog2e, -mxs));
+        s1 += __builtin_amdgcn_exp2f(fmaf(z[b * 32 + q + 1], kLog2e, -mxs));
       }
       st[b] = Stat{mx, s0 + s1};
     }
@@ -414,12 +413,12 @@ __global__ __launch_bounds__(T::NT, T::NT / 256) void score_gemm_kernel(ScoreGem
     float mx = p[0].x;
 #pragma unroll
     for (int q = 1; q < 8; ++q) mx = fmaxf(mx, p[q].x);
+    // (a partial without a finite logit has weight e^-inf = 0 and sum 0, or NaN,
+    // which stays)
     float sum = 0.f;
-    if (mx != -INFINITY) {
-      // (a partial without a finite logit has sum 0 and weight e^-inf = 0)
+    const float base = mx == -INFINITY ? 0.f : mx;
 #pragma unroll
-      for (int q = 0; q < 8; ++q) sum = fmaf(p[q].y, exp_e(p[q].x - mx), sum);
-    }
+    for (int q = 0; q < 8; ++q) sum = fmaf(p[q].y, exp_e(p[q].x - base), sum);
     reinterpret_cast<float2*>(g.part + (size_t)row * g.ntn + tni)[pass] = make_float2(mx, sum);
   }
 }

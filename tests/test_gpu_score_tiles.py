@@ -52,6 +52,31 @@ def test_score_tiles(n_seq, seq_len, K, V, r, dev):
         assert torch.equal(one["lp_on"], one["lp_off"])
 
 
+@pytest.mark.parametrize("M,two", [(40, False), (130, False), (520, False), (40, True)])
+def test_nan_logits_of_a_part_of_the_vocabulary_reach_every_row(M, two, dev):
+    """NaN in one block of 32 or 64 vocabulary rows: log-sum-exp and log-probabilities of every token are NaN, on every
+    tile, as with NaN anywhere else."""
+    import torch
+    say("score NaN", M, two)
+    V, K = 520, 64
+    for lo, hi in ((64, 128), (448, 520), (100, 101), (0, 64)):
+        s = WL.gen_score_head(8300 + M, 1, M, K, V, 16)
+        s.ids[:] = 300
+        W = dev_bf16(s.W_lm, dev).view(torch.bfloat16).clone()
+        W[lo:hi] = float("nan")
+        A, B, h = (dev_bf16(v, dev) for v in (s.A, s.B, s.h))
+        out = {k: torch.zeros(M, device=dev) for k in KEYS}
+        args = (W, A, B, s.s, torch.from_numpy(s.ids).to(dev), None, 1, M, out["lp_on"], out["lp_off"], out["kl"])
+        kw = dict(lse_on=out["lse_on"], lse_off=out["lse_off"])
+        if two:
+            H.hydra_score_two_input(h, h, *args, **kw)
+        else:
+            H.hydra_score(h, *args, **kw)
+        torch.cuda.synchronize()
+        for k in KEYS:
+            assert torch.isnan(out[k]).all(), (k, lo, hi)
+
+
 def test_tile_counts_of_any_remainder_keep_the_l2_order(dev):
     """500 tiles (no multiple of the eight XCDs) take the time of 496: each XCD walks neighbouring tiles either way."""
     import torch
