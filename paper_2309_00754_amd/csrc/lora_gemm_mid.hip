@@ -98,7 +98,12 @@ struct GemmMid {
   static constexpr int BSB = TN * RA * 2;                          // bytes of B's LDS copy
   static constexpr int NP = BSB + TM * 3 * RA * 2 + RED <= 160 * 1024 ? 3 : 2;
   static constexpr int TSB = TM * NP * RA * 2;                     // ... and of s T's
-  static constexpr size_t EPI = BSB + TSB + RED;
+  // Where all parts count, the second and third meet B without its infinities
+  // (FIN): the first part decides those outputs, as T itself would, and a part of
+  // the other sign, or none, would make them NaN.
+  static constexpr bool FIN = RA > 0 && TM < 32;
+  static constexpr int B2SB = FIN ? BSB : 0;
+  static constexpr size_t EPI = BSB + TSB + B2SB + RED;
   static constexpr size_t kLds = 160 * 1024 / WPC_;
   // fewer stages where they do not fit with the rows of A; an even number where
   // a slab is one k-step (its two fragment sets then alternate with the stages)
@@ -395,7 +400,8 @@ __global__ __launch_bounds__(G::NT, G::NT / 256) void lora_gemm_mid_kernel(MidAr
   char* const lds = reinterpret_cast<char*>(sm);
   uint16_t* const Bs = reinterpret_cast<uint16_t*>(lds);
   uint16_t* const Ts = reinterpret_cast<uint16_t*>(lds + G::BSB);
-  char* scratch = lds + G::BSB + G::TSB;
+  uint16_t* const Bfin = reinterpret_cast<uint16_t*>(lds + G::BSB + G::TSB);  // FIN: B, 0 for infinite and NaN
+  char* scratch = lds + G::BSB + G::TSB + G::B2SB;
   // PRE: the tile's rows of ts ([hi | lo], 2 rp values) and of bp (rp values)
   // go to LDS, swizzled like the slabs.  Read from memory per 32 x 32 block
   // they cost 576 KB a workgroup at rank 128 on 128 x 192, here 112 KB.  The
@@ -460,7 +466,10 @@ __global__ __launch_bounds__(G::NT, G::NT / 256) void lora_gemm_mid_kernel(MidAr
   if constexpr (RA > 0) {
 #pragma unroll
     for (int i = 0; i < BPT; ++i)
-      if (t + i * NT < TN * RA) Bs[t + i * NT] = (uint16_t)bv[i];
+      if (t + i * NT < TN * RA) {
+        Bs[t + i * NT] = (uint16_t)bv[i];
+        if constexpr (G::FIN) Bfin[t + i * NT] = (bv[i] & 0x7F80) == 0x7F80 ? 0 : (uint16_t)bv[i];
+      }
     // accT[q][j] holds T[trow + 16 q + 4 lg + e][16 j + l16] over this wave's k values
     float* tp = reinterpret_cast<float*>(scratch + (G::AT_ONCE ? G::EXB : 0));
 #pragma unroll
@@ -575,8 +584,9 @@ __global__ __launch_bounds__(G::NT, G::NT / 256) void lora_gemm_mid_kernel(MidAr
 #pragma unroll
         for (int ks = 0; ks < NP * RA / 16; ++ks) {
           const int k = ks * 16 + lh * 8;
+          const uint16_t* const bsrc = G::FIN && ks >= RA / 16 ? Bfin : Bs;
           const uint4 bf =
-              *reinterpret_cast<const uint4*>(Bs + (wc * WN + ((ni * 32 + l32) & G::WMASK)) * RA + k % RA1);
+              *reinterpret_cast<const uint4*>(bsrc + (wc * WN + ((ni * 32 + l32) & G::WMASK)) * RA + k % RA1);
           const uint4 tf =
               *reinterpret_cast<const uint4*>(Ts + (wr * WM + ((mi * 32 + l32) & G::XMASK)) * NP * RA + k);
           L = mfma32(bf, tf, L);

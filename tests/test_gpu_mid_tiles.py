@@ -179,3 +179,20 @@ def test_an_infinite_t_gives_infinite_outputs(dev):
     H.hydra_lora_linear(x, W, A, B, 2.0, None, y_on)
     torch.cuda.synchronize()
     assert (y_on[:, ::2] == float("-inf")).all() and (y_on[:, 1::2] == float("inf")).all()
+
+
+@pytest.mark.parametrize("M,N,K,r", [(12, 40, 64, 16), (9, 3000, 520, 64), (16, 9000, 72, 20)])
+def test_an_infinite_b_gives_infinite_outputs(M, N, K, r, dev):
+    """Up to 16 rows (x A^T) meets B in 24 bits, in parts: an infinity in B gives the infinity that the whole would."""
+    import torch
+    say("infinite b", M, N, K, r)
+    c = WL.gen_linear(9700 + N + r, M, K, N, r)
+    x, W, A, B = (dev_bf16(v, dev).view(torch.bfloat16).clone() for v in (c.x, c.W, c.A, c.B))
+    T = (x.double() @ A.double().t())[:, 3]
+    B[::2, 3], B[1::4, 3] = float("inf"), float("-inf")
+    y_on = _nan(M, N, dev)
+    H.hydra_lora_linear(x, W, A, B, 2.0, None, y_on)
+    torch.cuda.synchronize()
+    sign = torch.sign(T)[:, None].expand(M, N)
+    assert (y_on[:, ::2] == (sign * float("inf"))[:, ::2]).all() and (y_on[:, 1::4] == (-sign * float("inf"))[:, 1::4]).all()
+    assert torch.isfinite(y_on[:, 3::4]).all()
