@@ -304,7 +304,7 @@ HYDRA_PY(score, 20) {
     size_t bytes = 0;
     void* ws = own ? nullptr : a.workspace(v[16], bytes);
     int32_t* err = a.at1<int32_t>(v[17], kI32, 1);
-    a.ok = a.ok && W && n_seq >= 1 && seq_len >= 1 && n_seq <= M && n_seq * seq_len == M;
+    a.ok = a.ok && W && n_seq >= 1 && seq_len >= 1 && n_seq <= M && seq_len <= M && n_seq * seq_len == M;
     void* st = a.stream(v[18]);
     return [=]() {
       if (own)

@@ -98,7 +98,8 @@ def test_accepted_forms_have_the_bits_of_the_python_path(dev, monkeypatch):
         assert took.pop() != ("own workspace" in name or name in ("backward, dB only", "backward without adapter")), name
 
 
-@pytest.mark.parametrize("what", ["host", "dtype", "strided", "shape", "numpy", "no tensor", "scale", "workspace", "sizes"])
+@pytest.mark.parametrize("what", ["host", "dtype", "strided", "shape", "numpy", "no tensor", "scale", "workspace", "sizes",
+                                  "sizes past 64 bits"])
 def test_refused_forms_raise_what_the_python_path_raises(what, dev, monkeypatch):
     import torch
     c = WL.gen_linear(7500, 24, 264, 136, 8)
@@ -116,6 +117,8 @@ def test_refused_forms_raise_what_the_python_path_raises(what, dev, monkeypatch)
         "scale": lambda: H.hydra_lora_linear(x, W, A, B, "2", y),
         "workspace": lambda: H.hydra_score(x, W, A, B, 1.0, tok, None, 1, 24, v, v, v, workspace=True),
         "sizes": lambda: H.hydra_score(x, W, A, B, 1.0, tok, None, 2, 24, v, v, v, workspace=ws),
+        # 8 x (2^61 + 3) is 24, the rows of x, in 64 bits
+        "sizes past 64 bits": lambda: H.hydra_score(x, W, A, B, 1.0, tok, None, 8, 2 ** 61 + 3, v, v, v, workspace=ws),
     }[what]
     if what == "scale":  # a text that float() reads is taken by both
         call()
