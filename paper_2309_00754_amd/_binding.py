@@ -15,10 +15,12 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 from typing import Optional
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(PKG, "libhydra.so")
+NATIVE_PATH = os.path.join(PKG, "_hydra_native.so")
 
 HYDRA_OK = 0
 HYDRA_ERR_NULL = -1
@@ -167,7 +169,10 @@ def _native():
         _torch()
         try:
             from . import _hydra_native as nat
-        except ImportError:
+        except ImportError as e:
+            if os.path.exists(NATIVE_PATH):  # built, and yet not loaded: not to go unnoticed
+                warnings.warn(f"{NATIVE_PATH} does not load, calls go through ctypes and take longer on the host: "
+                              f"{e}", RuntimeWarning, stacklevel=3)
             nat = _NoNative()
         _nat = nat
     return _nat

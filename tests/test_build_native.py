@@ -1,9 +1,12 @@
-"""The native call path is a part that may be missing: libhydra.so is built without it."""
+"""The native call path is a part that may be missing: libhydra.so is built without it, and its absence is said."""
 import os
+import sys
 import warnings
 
 import pytest
 
+import paper_2309_00754_amd as H
+from paper_2309_00754_amd import _binding as Bd
 from paper_2309_00754_amd import build as Bu
 
 
@@ -30,3 +33,18 @@ def test_libhydra_is_built_without_the_native_binding(where, tmp_path, monkeypat
     ok = where == "nowhere"
     assert os.path.exists(Bu.NATIVE) == ok
     assert ["no torch headers" in str(w.message) for w in said] == ([] if ok else [True])
+
+
+@pytest.mark.parametrize("built", [True, False])
+def test_a_built_binding_that_does_not_load_is_said_once(built, tmp_path, monkeypatch):
+    path = tmp_path / "_hydra_native.so"
+    if built:
+        path.touch()
+    monkeypatch.setattr(Bd, "NATIVE_PATH", str(path))
+    monkeypatch.setattr(Bd, "_nat", None)
+    monkeypatch.delattr(H, "_hydra_native", raising=False)
+    monkeypatch.setitem(sys.modules, "paper_2309_00754_amd._hydra_native", None)  # its import raises ImportError
+    with warnings.catch_warnings(record=True) as said:
+        warnings.simplefilter("always")
+        assert isinstance(Bd._native(), Bd._NoNative) and isinstance(Bd._native(), Bd._NoNative)
+    assert ["does not load" in str(w.message) for w in said] == [True] * built
