@@ -46,7 +46,7 @@ struct MidArgs {
   int kch[kMaxGroup];
   int nkc[kMaxGroup];
   int ntm, ntn;                   // tiles of one member
-  int total, first;               // workgroups in all, and of the launches before this one
+  int total;                      // workgroups
   int vec4;                       // outputs may be written with 16-byte stores
 };
 
@@ -155,7 +155,7 @@ __global__ __launch_bounds__(G::NT, G::NT / 256) void lora_gemm_mid_kernel(MidAr
   // on one L2).
   int gi, tmi, tni, kc = 0;
   {
-    const int tiles = g.ntm * g.ntn, total = g.total, bid = g.first + blockIdx.x;
+    const int tiles = g.ntm * g.ntn, total = g.total, bid = blockIdx.x;
     const int q = total >> 3, rem = total & 7, xcd = bid & 7;
     int lid = xcd * q + min(xcd, rem) + (bid >> 3);
     gi = lid / tiles;
@@ -643,7 +643,7 @@ float tile_cost(const MidTile& c, int M, int N, int K) {
 }
 
 template <class G, MidMode MODE, bool FOLD = false>
-void launch_tile(MidArgs& g, hipStream_t stream) {
+hipError_t launch_tile(MidArgs& g, hipStream_t stream) {
   int members = g.ga.G;  // (member, chunk) pairs of the pre-pass
   if constexpr (MODE == PART) {
     members = 0;
@@ -651,21 +651,20 @@ void launch_tile(MidArgs& g, hipStream_t stream) {
   }
   g.ntm = (g.ga.M + G::TM - 1) / G::TM;
   g.ntn = (g.ga.N + G::TN - 1) / G::TN;
-  // a dispatch counts the work-items of a dimension in 32 bits: the largest
-  // grids take several launches (of a multiple of 8 workgroups: the XCD of a
-  // workgroup follows from its number).  A second grid dimension with a test for
-  // the surplus workgroups cost every call: 16 x 512 x 512 4.96 -> 5.21 us.
-  g.total = g.ntm * g.ntn * members;
-  for (g.first = 0; g.first < g.total; g.first += 1 << 22)
-    hipLaunchKernelGGL((lora_gemm_mid_kernel<G, MODE, FOLD>), dim3(std::min(g.total - g.first, 1 << 22)), dim3(G::NT), 0,
-                       stream, g);
+  // A dispatch counts its work-items in 32 bits.  The rule gives these tiles at
+  // most about 2^19 workgroups, 8 members or jobs (larger outputs take 128 x 256).
+  const int64_t total = (int64_t)g.ntm * g.ntn * members;
+  if (total * G::NT >= (int64_t(1) << 32)) return hipErrorInvalidValue;
+  g.total = (int)total;
+  hipLaunchKernelGGL((lora_gemm_mid_kernel<G, MODE, FOLD>), dim3(g.total), dim3(G::NT), 0, stream, g);
+  return hipGetLastError();
 }
 
 template <class G>
-void launch_plain(MidArgs& g, hipStream_t stream) {
+hipError_t launch_plain(MidArgs& g, hipStream_t stream) {
   if constexpr (G::TM == kFewRows)
     if (g.ga.K > kFoldSlabs * G::BK) return launch_tile<G, PLAIN, true>(g, stream);
-  launch_tile<G, PLAIN>(g, stream);
+  return launch_tile<G, PLAIN>(g, stream);
 }
 
 // Workgroups per CU that the ring leaves room for: two on the 16-row tiles
@@ -677,27 +676,17 @@ constexpr int per_cu(int tm, int tn, int ra) {
 
 template <int TM, int TN, int WM, int WN, int KS, int BK, int NS>
 hipError_t launch_mid(MidArgs& g, int ra, hipStream_t stream) {
-  if constexpr (TM != kFewRows) {
-    if (g.nkc[0] > 0) {
-      launch_tile<GemmMid<TM, TN, WM, WN, KS, BK, NS, 1, 0>, PART>(g, stream);
-      return hipGetLastError();
-    }
-    if (g.rp > 0) {
-      launch_tile<GemmMid<TM, TN, WM, WN, KS, BK, NS, 1, 0>, PRE>(g, stream);
-      return hipGetLastError();
-    }
+  if constexpr ((TM == 64 && TN == 64) || (TM == 128 && TN == 128))  // the pre-pass's own tiles
+    if (g.nkc[0] > 0) return launch_tile<GemmMid<TM, TN, WM, WN, KS, BK, NS, 1, 0>, PART>(g, stream);
+  if constexpr (TM != kFewRows)
+    if (g.rp > 0) return launch_tile<GemmMid<TM, TN, WM, WN, KS, BK, NS, 1, 0>, PRE>(g, stream);
+  switch (ra) {
+    case 0: return launch_plain<GemmMid<TM, TN, WM, WN, KS, BK, NS, per_cu(TM, TN, 0), 0>>(g, stream);
+    case 16: return launch_plain<GemmMid<TM, TN, WM, WN, KS, BK, NS, per_cu(TM, TN, 16), 16>>(g, stream);
+    case 32: return launch_plain<GemmMid<TM, TN, WM, WN, KS, BK, NS, per_cu(TM, TN, 32), 32>>(g, stream);
+    case 64: return launch_plain<GemmMid<TM, TN, WM, WN, KS, BK, NS, per_cu(TM, TN, 64), 64>>(g, stream);
+    default: return hipErrorInvalidValue;
   }
-  if (ra == 0)
-    launch_plain<GemmMid<TM, TN, WM, WN, KS, BK, NS, per_cu(TM, TN, 0), 0>>(g, stream);
-  else if (ra == 16)
-    launch_plain<GemmMid<TM, TN, WM, WN, KS, BK, NS, per_cu(TM, TN, 16), 16>>(g, stream);
-  else if (ra == 32)
-    launch_plain<GemmMid<TM, TN, WM, WN, KS, BK, NS, per_cu(TM, TN, 32), 32>>(g, stream);
-  else if (ra == 64)
-    launch_plain<GemmMid<TM, TN, WM, WN, KS, BK, NS, per_cu(TM, TN, 64), 64>>(g, stream);
-  else
-    return hipErrorInvalidValue;
-  return hipGetLastError();
 }
 
 hipError_t launch_any(MidArgs& g, int ra, int tile, hipStream_t stream) {
