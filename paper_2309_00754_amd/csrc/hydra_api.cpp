@@ -488,8 +488,7 @@ hydra_status score_check(const uint16_t* h, const uint16_t* W_lm, const uint16_t
   if (n_seq > kMaxDim / seq_len) return HYDRA_ERR_SHAPE;
   const int64_t M = n_seq * seq_len;
   if (M > kMaxRows || V > kMaxCols) return HYDRA_ERR_SHAPE;
-  if (!grid_ok(cdiv(M, hydra::kScoreTileM) * cdiv(V, hydra::kScoreTileN), hydra::kScoreThreads))
-    return HYDRA_ERR_SHAPE;
+  if (cdiv(M, hydra::kScoreTileM) * cdiv(V, hydra::kScoreTileN) >= hydra::kScoreMaxTiles) return HYDRA_ERR_SHAPE;
   if (r < 0 || r > HYDRA_MAX_RANK) return HYDRA_ERR_SHAPE;
   if (r > 0 && (!A || !B)) return HYDRA_ERR_NULL;
   if (!aligned(h, 16) || !aligned(W_lm, 16)) return HYDRA_ERR_ALIGN;
@@ -633,8 +632,7 @@ hydra_status hydra_score_two_input(const uint16_t* h_act, const uint16_t* h_off,
   if (chk != HYDRA_OK) return chk;
   const int64_t M = n_seq * seq_len;
   // twice the row tiles of the one-input pass
-  if (!grid_ok(2 * cdiv(M, hydra::kScoreTileM) * cdiv(V, hydra::kScoreTileN), hydra::kScoreThreads))
-    return HYDRA_ERR_SHAPE;
+  if (2 * cdiv(M, hydra::kScoreTileM) * cdiv(V, hydra::kScoreTileN) >= hydra::kScoreMaxTiles) return HYDRA_ERR_SHAPE;
   if (!aligned(h_act, 16)) return HYDRA_ERR_ALIGN;
   if (!workspace) return HYDRA_ERR_WORKSPACE;
   if (workspace_bytes < score_ws_bytes(M, V)) return HYDRA_ERR_WORKSPACE;

@@ -80,9 +80,10 @@ struct TpreArgs {
   // both, which the choice of kernel and chunks looks at (0: K)
   int Kform, Kall;
 };
-// K is split into at most kTpreMaxChunks chunks of at least 1024, so that
-// the pre-pass spreads over many workgroups; the partial products are then
-// added in chunk order (deterministic).
+// K is split into at most kTpreMaxChunks chunks, so that the pre-pass spreads
+// over many workgroups; the partial products are then added in chunk order
+// (deterministic).  At padded ranks 16 and 32 the chunks are of at least 1024
+// (below); launch_t_part_mid chooses those of 64 and 128.
 constexpr int kTpreMaxChunks = 8;
 inline void tpre_chunks(int K, int& nkc, int& kch) {
   const int want = (K + 1023) / 1024;
@@ -216,10 +217,13 @@ hipError_t launch_lora_gemm_slabs(const LinearArgs& a, const uint16_t* ts, const
 // Column-tile width of the fused scoring GEMM (number of vocabulary entries
 // one workgroup reduces).
 constexpr int kScoreTileN = 256;
-// Launch shapes the host validation needs: a dispatch counts work-items in
-// 32 bits, so (tiles x threads per workgroup) must stay below 2^32.
+// Limits of the host validation.  Scoring: tiles of kScoreTileM rows, all inputs
+// together (the kernel numbers its tiles, up to four times as many on its smaller
+// ones, in an int; what one dispatch cannot count is a second grid dimension).
 constexpr int kScoreTileM = 256;
-constexpr int kScoreThreads = 256;
+constexpr int64_t kScoreMaxTiles = int64_t(1) << 24;
+// The dual GEMM: a dispatch counts work-items in 32 bits, so (tiles x threads
+// per workgroup) must stay below 2^32.
 constexpr int kGemmTileM = 128;
 constexpr int kGemmTileN = 256;
 constexpr int kGemmThreads = 512;
@@ -238,7 +242,7 @@ hipError_t launch_lora_gemm_mid(const GroupArgs& ga, const uint16_t* const* ts, 
                                 int tile, hipStream_t stream);
 // Partial T over K chunks of the pre-pass jobs (same M; padded rank 64 or 128)
 // on those tiles, one launch; nkc[j] receives the number of chunks written to
-// as[j].part, which depends on M, K and rp alone.
+// as[j].part, which depends on M, rp, and K, Kform and Kall alone.
 hipError_t launch_t_part_mid(const TpreArgs* as, int n, int rp, int* nkc, hipStream_t stream);
 hipError_t launch_lora_gemm(const LinearArgs& a, hipStream_t stream);
 // The same with the LoRA update from the pre-pass: ts [M x 2 RP] and bp [N x RP]

@@ -101,3 +101,29 @@ def test_tile_counts_of_any_remainder_keep_the_l2_order(dev):
 
     any_count, by_eight = us(32000), us(31744)
     assert any_count < 1.15 * by_eight, (any_count, by_eight)
+
+
+def test_more_tiles_than_one_dispatch_counts(dev):
+    """2 x 2048 x 1025 tiles: more than 2^22, so that the grid takes a second dimension with surplus workgroups.  Every
+    1021st row, and the last ones, against float64."""
+    import torch
+    say("score, split grid")
+    M, V, K = 2048 * 256, 1025 * 256 - 7, 8
+    g = torch.Generator(device=dev).manual_seed(8400)
+    h, ha = (torch.randn(M, K, generator=g, device=dev).to(torch.bfloat16) for _ in range(2))
+    W = torch.randn(V, K, generator=g, device=dev).to(torch.bfloat16)
+    tok = torch.randint(0, V, (M,), generator=g, device=dev, dtype=torch.int32)
+    out = [torch.full((M,), float("nan"), device=dev) for _ in range(3)]
+    H.hydra_score_two_input(ha, h, W, None, None, 1.0, tok, None, 1, M, *out)
+    torch.cuda.synchronize()
+    rows = torch.cat([torch.arange(0, M, 1021), torch.arange(M - 300, M)]).to(dev)
+    want = []
+    for x in (ha, h):
+        lp = []
+        for r in rows.split(64):
+            z = x[r].double() @ W.double().t()
+            lp.append(z.gather(1, tok[r].long()[:, None])[:, 0] - torch.logsumexp(z, 1))
+        want.append(torch.cat(lp).cpu().numpy())
+    for got, e, k in zip(out, (want[0], want[1], want[0] - want[1]), ("lp_on", "lp_off", "kl")):
+        assert torch.isfinite(got).all()
+        assert_abs(host(got[rows]), e, k)
