@@ -1,29 +1,43 @@
 """The dual GEMM's smaller tiles (9 rows to a few hundred): edges of every tile, K shorter than a slab and longer than
 the ring, every way the LoRA update reaches them, against the float64 oracle; and the bits that the entry points share.
 Tolerances: the arithmetic bound of the other linear tests (2e-4 relative)."""
+import ctypes
+
 import numpy as np
 import pytest
 
 import paper_2309_00754_amd as H
+from paper_2309_00754_amd import _binding as Bd
 import workloads as WL
 from oracle import lora_linear_ref
 from gpu_helpers import assert_rel, dev_bf16, host, say
 
 pytestmark = pytest.mark.gpu
 
-# (M, N, K) by the tile that the size model picks: one with remainders in both directions, one of whole tiles
-SHAPES = [
-    (9, 40, 264), (16, 512, 512), (17, 33, 8), (31, 700, 72), (64, 96, 1536),  # 32 x 32
-    (65, 5000, 264), (96, 4096, 128),                         # 32 x 64
-    (40, 8200, 136), (128, 8192, 1032),                       # 64 x 64
-    (200, 5000, 264), (300, 5001, 1000), (128, 16384, 128),   # 64 x 128
-    (230, 11000, 520), (256, 8192, 2048),                     # 128 x 128
-    (129, 16500, 72), (400, 11001, 520), (384, 12288, 256),   # 128 x 192
-]
+# (M, N, K) by the tile that the size model picks (-1: up to 16 rows, whose tiles go by rank and members too): with
+# remainders in both directions, and of whole tiles
+SHAPES = {
+    -1: [(9, 40, 264), (16, 512, 512)],                                    # 16 rows
+    0: [(17, 33, 8), (31, 700, 72), (64, 96, 1536)],                       # 32 x 32
+    1: [(65, 5000, 264), (96, 4096, 128)],                                 # 32 x 64
+    2: [(40, 8200, 136), (128, 8192, 1032)],                               # 64 x 64
+    3: [(200, 5000, 264), (300, 5001, 1000), (128, 16384, 128), (256, 8192, 2048)],  # 64 x 128
+    4: [(230, 11000, 520), (384, 8192, 1536)],                             # 128 x 128
+    5: [(129, 16500, 72), (400, 11001, 520), (384, 12288, 256)],           # 128 x 192
+}
 
 
-def _inputs(M, N, K, r, dev):
-    c = WL.gen_linear(9000 + M + 3 * N + 7 * K + r, M, K, N, r)
+def test_shapes_go_to_the_tiles_they_are_listed_under():
+    import torch  # noqa: F401 (its HIP runtime first: the library is to find that one)
+    pick = ctypes.CDLL(Bd.LIB_PATH)["_ZN5hydra13gemm_mid_tileEiii"]
+    pick.argtypes, pick.restype = [ctypes.c_int] * 3, ctypes.c_int
+    for tile, shapes in SHAPES.items():
+        for s in shapes:
+            assert (pick(*s) == tile) if tile >= 0 else s[0] <= 16, (s, pick(*s))
+
+
+def _inputs(M, N, K, r, dev, member=0):
+    c = WL.gen_linear(9000 + M + 3 * N + 7 * K + r + 100000 * member, M, K, N, r)
     x, W = dev_bf16(c.x, dev), dev_bf16(c.W, dev)
     return c, x, W, dev_bf16(c.A, dev) if r else None, dev_bf16(c.B, dev) if r else None
 
@@ -34,7 +48,7 @@ def _nan(M, N, dev):
 
 
 @pytest.mark.parametrize("r", [0, 8, 16, 20, 64, 100])
-@pytest.mark.parametrize("M,N,K", SHAPES)
+@pytest.mark.parametrize("M,N,K", sum(SHAPES.values(), []))
 def test_mid_tiles(M, N, K, r, dev):
     import torch
     say("mid tile", M, N, K, r)
@@ -69,8 +83,8 @@ def test_mid_group_members_have_the_bits_of_single_calls(M, N, K, r, dev):
     import torch
     say("mid group", M, N, K, r)
     G = 4
-    ms = [_inputs(M, N, K + 0 * i, r, dev) for i in range(G)]
-    xs, Ws = [m[1] for m in ms], [torch.roll(m[2], i, 0) for i, m in enumerate(ms)]
+    ms = [_inputs(M, N, K, r, dev, i) for i in range(G)]
+    xs, Ws = [m[1] for m in ms], [m[2] for m in ms]
     As, Bs = [m[3] for m in ms], [m[4] for m in ms]
     ss = [2.0, -0.5, 1.0, 3.0]
     offs = [_nan(M, N, dev), None, _nan(M, N, dev), _nan(M, N, dev)]

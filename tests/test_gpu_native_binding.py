@@ -114,14 +114,22 @@ def test_refused_forms_raise_what_the_python_path_raises(what, dev, monkeypatch)
         "shape": lambda: H.hydra_lora_linear(x, W, A, B[:-1], 1.0, y),
         "numpy": lambda: H.hydra_lora_linear_group([c.x], [W], [A], [B], [1.0], [y]),
         "no tensor": lambda: H.hydra_value_head(None, x[0], v),
-        "scale": lambda: H.hydra_lora_linear(x, W, A, B, "2", y),
+        "scale": None,
         "workspace": lambda: H.hydra_score(x, W, A, B, 1.0, tok, None, 1, 24, v, v, v, workspace=True),
         "sizes": lambda: H.hydra_score(x, W, A, B, 1.0, tok, None, 2, 24, v, v, v, workspace=ws),
         # 8 x (2^61 + 3) is 24, the rows of x, in 64 bits
         "sizes past 64 bits": lambda: H.hydra_score(x, W, A, B, 1.0, tok, None, 8, 2 ** 61 + 3, v, v, v, workspace=ws),
     }[what]
-    if what == "scale":  # a text that float() reads is taken by both
-        call()
+    if what == "scale":  # a text that float() reads is taken by both, as the number
+        got = []
+        for path in (Bd._native(), Bd._NoNative()):
+            monkeypatch.setattr(Bd, "_nat", path)
+            on = torch.full((24, 136), float("nan"), device=dev)
+            H.hydra_lora_linear(x, W, A, B, "2", None, on)
+            got.append(on)
+        H.hydra_lora_linear(x, W, A, B, 2.0, None, y)
+        torch.cuda.synchronize()
+        assert torch.equal(got[0], y) and torch.equal(got[1], y)
         return
     kinds = []
     for path in (Bd._native(), Bd._NoNative()):
