@@ -79,11 +79,11 @@ typedef enum {
  * At least one output must be non-NULL.  Requires 1 <= M <= 2^20, 1 <= N <= 2^21,
  * K >= 1, K % 8 == 0, K <= 2^21, 0 <= r <= HYDRA_MAX_RANK, and
  * ceil(M / 128) * ceil(N / 256) < 2^23 (the GEMM's tile grid fits one
- * dispatch; roughly M * N < 2^38).  With r == 0, y_on equals
- * y_off.  M <= 8 (at r > 64 M <= 16) selects the bandwidth-bound (decode)
- * kernels, larger M the MFMA GEMM; both compute the same function.  At M > 16 with y_on and r > 64
- * the update needs the pre-pass workspace of hydra_lora_linear_ws: this call
- * then returns HYDRA_ERR_WORKSPACE and launches nothing.
+ * dispatch; roughly M * N < 2^38).  With r == 0, y_on equals y_off.  M <= 8
+ * (with y_on and r > 64 M <= 16) selects the bandwidth-bound (decode) kernels,
+ * larger M the MFMA GEMM; both compute the same function.  At M > 16 with y_on
+ * and r > 64 the update needs the pre-pass workspace of hydra_lora_linear_ws:
+ * this call then returns HYDRA_ERR_WORKSPACE and launches nothing.
  */
 hydra_status hydra_lora_linear(const uint16_t* x, const uint16_t* W, const uint16_t* A, const uint16_t* B,
                                float s, int64_t M, int64_t N, int64_t K, int64_t r,
@@ -100,13 +100,16 @@ hydra_status hydra_lora_linear_workspace_bytes(int64_t M, int64_t N, int64_t r, 
 /*
  * hydra_lora_linear_ws -- hydra_lora_linear with a caller-provided workspace,
  * which lets the MFMA GEMM (M > 16) take the LoRA update from a pre-pass:
- * s x A^T is computed once per row (instead of once per 256-column tile) as
- * bf16 hi and lo parts, and added with B as 2 RP more k values of the GEMM
- * (RP = r rounded up to 16, 32, 64 or 128) after y_off has been stored.
- * This is the path for the paper's rank 128 (App. B), and the faster one
- * above rank 16, where the in-tile product of hydra_lora_linear adds RP / 256
- * of the base GEMM's work; at rank 16 the pre-pass costs about what the GEMM
- * saves.  Defined by: the same passages as hydra_lora_linear.
+ * s x A^T is computed once per row (instead of once per column tile) as bf16
+ * hi and lo parts, and added with B as 2 RP more k values of the GEMM (RP = r
+ * rounded up to 16, 32, 64 or 128).  This is the path for the paper's rank 128
+ * (App. B), and on the GEMM's largest tile (128 x 256) the faster one above
+ * rank 16, where the in-tile product of hydra_lora_linear adds RP / 256 of the
+ * base GEMM's work; at rank 16 the pre-pass costs about what the GEMM saves.
+ * On the smaller tiles, which small M * N take, ranks up to 64 are formed in
+ * the tile as by hydra_lora_linear (rank 64 in several rounds of 128 x 192
+ * tiles excepted) and the workspace is checked and not used.  Defined by: the
+ * same passages as hydra_lora_linear.
  *
  *   workspace, workspace_bytes   device memory of at least
  *       hydra_lora_linear_workspace_bytes(M, N, r) bytes, 16-byte aligned,
@@ -137,10 +140,12 @@ hydra_status hydra_lora_linear_ws(const uint16_t* x, const uint16_t* W, const ui
  *                         or hold NULL entries
  *   s                     HOST array of G scales
  * Member i computes exactly what hydra_lora_linear(x[i], W[i], A[i], B[i], s[i],
- * M, N, K, r, y_off[i], y_on[i]) computes.  Each member needs at least one
- * output.  M <= 8 runs one launch for the whole group; larger M one launch
- * too where the GEMM takes its smaller tiles, else the GEMM once per member.  Errors as in hydra_lora_linear; HYDRA_ERR_SHAPE for G out
- * of range.
+ * M, N, K, r, y_off[i], y_on[i]) computes (to rounding where M is 9 to 16,
+ * r > 64 and only other members have y_on: the member's own call would take
+ * the GEMM).  Each member needs at least one output.  M <= 8 runs one launch
+ * for the whole group; larger M one launch too where the GEMM takes its smaller
+ * tiles, else the GEMM once per member.  Errors as in hydra_lora_linear;
+ * HYDRA_ERR_SHAPE for G out of range.
  */
 hydra_status hydra_lora_linear_group(int64_t G, const uint16_t* const* x, const uint16_t* const* W,
                                      const uint16_t* const* A, const uint16_t* const* B, const float* s,
@@ -474,8 +479,9 @@ hydra_status hydra_ppo_advantages(const float* kl, const float* reward, const fl
  *   d_lp [M] fp32             out, optional: d policy loss / d lp_new (-rho A / n where the
  *                             unclipped term is the minimum, else 0; 0 before start)
  *   d_v [M] fp32              out, optional: d value loss / d V ((V - R) / n; 0 before start)
- * One workgroup sums in a fixed order (deterministic).  No output may be an
- * input or another output (HYDRA_ERR_SHAPE); buffers 4-byte aligned.
+ * One workgroup per loss sums in a fixed order (deterministic), beside others
+ * that write the gradients: no output may be an input or another output
+ * (HYDRA_ERR_SHAPE).  Buffers 4-byte aligned; 16-byte aligned ones are faster.
  * Requires n_seq, seq_len >= 1 and M = n_seq * seq_len <= 2^20.
  */
 hydra_status hydra_ppo_loss(const float* lp_new, const float* lp_old, const float* advantages, const float* values,

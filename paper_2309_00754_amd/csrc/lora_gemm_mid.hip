@@ -6,9 +6,10 @@
 //
 // What bounds a small tile is the copy of its operands into LDS (about
 // 64 B/clk per CU) and the latency of each K slab, not the matrix cores.  So:
-//  * one workgroup of 8 waves per tile; the waves that share a sub-tile split
-//    every K slab among them (KS ways), which keeps the sub-tile of a wave, and
-//    with it the number of MFMAs per LDS byte, large on a small tile;
+//  * one workgroup of 8 waves (4 up to 32 x 64) per tile; the waves that share a
+//    sub-tile split every K slab among them (KS ways), which keeps the sub-tile
+//    of a wave, and with it the number of MFMAs per LDS byte, large on a small
+//    tile;
 //  * every wave issues its share of the copies (buffer_load ... lds) for the
 //    slab NS ahead, reads the fragments of the next slab from LDS into a second
 //    register set, and runs the MFMAs of the current one between them; one
@@ -22,9 +23,9 @@
 //    parts of s T and the padded rows of B are read from the pre-pass's
 //    workspace.
 // The K order of every output depends on the tile shape alone, and the shape
-// on M, N and K alone, so an output has the same bits whatever the entry point.
-#include <algorithm>
-
+// on M, N and K alone (up to 16 rows on the rank and the members too, among
+// shapes of one K order), so an output has the same bits whatever the entry
+// point that comes here.
 #include "hydra_device.h"
 #include "hydra_internal.h"
 
@@ -619,11 +620,21 @@ __global__ __launch_bounds__(G::NT, G::NT / 256) void lora_gemm_mid_kernel(MidAr
 // end of a tile's last round): base + rounds x (fixed + slabs x step), rounds
 // of 256 tiles (one workgroup per CU) and slabs of 64 k values.  The numbers
 // are fits to kernel times over M = 17 ... 4096 and eight (K, N) from 700 to
-// 11008 at rank 16 (rms error 11-18%; the model's choice is 0.4% slower than
-// the best one on average, 16% at most).
-// What they say: a 64-wide slab of a tile costs its bytes at 66
-// to 74 GB/s per CU whatever the tile, so a larger one is cheaper per output as
-// long as it still gives 256 tiles.
+// 11008 at rank 16 (rms error 11-18%).  What they say: a 64-wide slab of a tile
+// costs its bytes at 66 to 74 GB/s per CU whatever the tile, so a larger one is
+// cheaper per output as long as it still gives 256 tiles.
+// Checked at ranks 0, 16, 32, 64 and 128 over 32 row counts from 17 to 4096 and 13
+// (K, N), against the best tile: 0.2, 0.05, 0.03, 0.7 and 0.2% slower on average;
+// against the 128 x 256 tile alone 0.46 to 0.55 of its time on average, in no case
+// longer at ranks 32 and 64, in 18 of 1248 at the others by 1 to 7%.  Those take
+// 128 x 192 tiles, either in one nearly full round with all operands in the
+// last-level cache (1400 x 4096 x 4096 rank 0 46.9 -> 49.2 us; weights from memory
+// 58.6 -> 53.0) or in several rounds, where at K = 1504 to 4096 the two tiles
+// differ by 11% either way in an order that counts of tiles, rounds and bytes do
+// not explain (rank 16, 2560 x 1504 x 7000 110 -> 122, 2560 x 4096 x 4096 115 ->
+// 119, 1816 x 3000 x 6000 143 -> 127).  Members of a group, whose rounds run
+// together, gain up to 18% there (four 1400 x 3000 x 6000 rank 128 535 -> 440),
+// and a member's outputs have the bits of its own call: the rule is one for both.
 // M x K x N, us: 48 x 4096 x 4096 41.4 -> 11.6, 333 x 4096 x 11008 72 -> 58,
 // 512 x 4096 x 4096 47.6 -> 29.9, 1000 x 11008 x 4096 157 -> 121, 500 x 2048 x
 // 2048 30.2 -> 13.6 (128 x 256 tile -> here, rank 16).
