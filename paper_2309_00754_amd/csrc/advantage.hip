@@ -214,14 +214,16 @@ constexpr int PL_BATCH = 4;  // groups of four tokens per thread requested befor
 // left over are taken one by one; else tokens t, t + 1024, ... of the block, so
 // that the lanes of a 4-byte load stay side by side (46 x 1659 tokens, four
 // neighbouring tokens a thread in 4-byte loads 53.8 us, so 18.5, VEC 13.9).
-template <bool VEC>
+// REST: there are such tokens (a kernel of its own: the code for them costs a
+// small call 0.2 us).
+template <bool VEC, bool REST>
 __global__ __launch_bounds__(PL_THREADS) void ppo_loss_kernel(PpoLossArgs a) {
   __shared__ float red[2][PL_THREADS / 64];
   constexpr int BLOCK = PL_THREADS * 4;
   const int t = threadIdx.x;
   const int T = a.seq_len;
   const int M = a.n_seq * T;
-  const int Mv = VEC ? M & ~3 : M;  // tokens taken in groups
+  const int Mv = REST ? M & ~3 : M;  // tokens taken in groups
   const float inv_n = 1.f / ((float)a.n_seq * (float)(T - a.start));
   const float lo_b = 1.f - a.eps, hi_b = 1.f + a.eps;
   // token i of this thread's group in the block from b on
@@ -272,7 +274,7 @@ __global__ __launch_bounds__(PL_THREADS) void ppo_loss_kernel(PpoLossArgs a) {
     return un <= cl ? -un * inv_n : 0.f;
   };
 
-  const bool left = VEC && Mv < M && t < M - Mv;  // this thread takes the left-over token Mv + t
+  const bool left = REST && t < M - Mv;  // this thread takes the left-over token Mv + t
   auto is_response = [&](int m) __attribute__((always_inline)) { return m % T >= a.start; };
 
   if (blockIdx.x >= 2) {
@@ -370,10 +372,12 @@ hipError_t launch_ppo_loss(const PpoLossArgs& a, hipStream_t stream) {
   for (const void* p : ps) vec = vec && (reinterpret_cast<uintptr_t>(p) & 15) == 0;
   const int M = a.n_seq * a.seq_len;
   const int grads = a.d_lp || a.d_v ? (M + PL_THREADS * 4 - 1) / (PL_THREADS * 4) : 0;
-  if (vec)
-    hipLaunchKernelGGL(ppo_loss_kernel<true>, dim3(2 + grads), dim3(PL_THREADS), 0, stream, a);
+  if (!vec)
+    hipLaunchKernelGGL((ppo_loss_kernel<false, false>), dim3(2 + grads), dim3(PL_THREADS), 0, stream, a);
+  else if (M % 4 != 0)
+    hipLaunchKernelGGL((ppo_loss_kernel<true, true>), dim3(2 + grads), dim3(PL_THREADS), 0, stream, a);
   else
-    hipLaunchKernelGGL(ppo_loss_kernel<false>, dim3(2 + grads), dim3(PL_THREADS), 0, stream, a);
+    hipLaunchKernelGGL((ppo_loss_kernel<true, false>), dim3(2 + grads), dim3(PL_THREADS), 0, stream, a);
   return hipGetLastError();
 }
 
